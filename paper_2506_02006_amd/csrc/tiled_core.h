@@ -28,15 +28,18 @@ struct TiledTail {
 // that is a multiple of 4.)  Assembly, because the compiler would wait for all of them before any read of LDS; it does
 // not see these loads, and the waits are wait_vm() below, counted by hand.  A load or a reload from scratch memory that the
 // compiler adds only makes those waits longer.
+// s_nop 4: a vector instruction that writes a scalar register and a memory instruction that reads it need five wait states between them.  The
+// compiler keeps them for its own loads and does not look in here, and it brings descriptor words and offsets that it has parked in vector lanes back with
+// v_readlane right before the block.  The five states also cover the one that m0 needs.
 template <bool NT>
 __device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, u32x4 rsrc, uint32_t soff)
 {
-    if constexpr (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-    else              asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    if constexpr (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    else              asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 __device__ __forceinline__ void dma4(uint32_t lds, uint32_t voff, u32x4 rsrc, uint32_t soff)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 // until at most N of this wave's loads are outstanding (they return in order)
 template <int N>
