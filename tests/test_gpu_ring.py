@@ -118,7 +118,7 @@ def test_workspace_of_the_older_kernels(B, kind):
     tag = {"dense": B.KIND_FP16, "w4": B.KIND_W4A16, "w8": B.KIND_W8A16}[kind]
     fn = {"dense": B.linear_fp16, "w4": B.linear_w4a16, "w8": B.linear_w8a16}[kind]
     taken = 0
-    for M, K, N in ((160, 2048, 6144), (100, 2048, 2048), (320, 3072, 9216), (72, 3072, 8192)):
+    for M, K, N in ((160, 2048, 6144), (100, 2048, 2048), (320, 3072, 9216), (72, 3072, 8192), (320, 4096, 9216)):   # (the last: codes on the ring with K split)
         B.set_tuning(B.TUNE_TILED, 1)
         try:
             p = Problem(B, kind, 0, M, K, N)
@@ -134,3 +134,34 @@ def test_workspace_of_the_older_kernels(B, kind):
         assert any(same)
         taken += same[0] and not torch.equal(older, ring)
     assert taken, "no shape where the older kernels stood in for the ring"
+
+
+@pytest.mark.parametrize("kind", ["w4", "w8"])
+@pytest.mark.parametrize("bf", [0, 1])
+@pytest.mark.parametrize("M,K,N", [(65, 2048, 6144), (100, 14336, 4096), (160, 2048, 6144), (256, 4096, 4096)])
+def test_codes_beyond_64_rows_stay_exact(B, kind, bf, M, K, N):
+    """Where codes are multiplied as they are, y is the 16-bit rounding of a sum with fp32 errors only: relative to |y| these add up like a walk of
+    at most K steps of 2^-25, 2^-18 for the largest K here, so that a rounding to 16 bits (steps of 2^-10 .. 2^-11 of y in fp16, eight times that in
+    bfloat16) goes another way in about 2 * 2^-18 / 2^-11 = 1.6 % of the elements; zero points taken off large sums may triple that.  Weights rounded
+    to 16 bits (2^-12 of y and more) change a quarter of them and more."""
+    print(f"exact codes {kind} bf={bf} M={M} K={K} N={N}", flush=True)
+    p = Problem(B, kind, bf, M, K, N)
+    y = p.run()
+    share = float((y != p.ref.to(y.dtype)).double().mean())
+    assert share <= 0.05, share
+
+
+@pytest.mark.parametrize("kind", ["w4", "w8"])
+def test_weights_beyond_the_fp16_range(B, kind):
+    """Masters of up to 3e5 (the format's scales allow it) and small rows: the products stay in range, so the results are finite and right."""
+    M, K, N = 100, 4096, 4096
+    g = torch.Generator(device="cuda").manual_seed(synth.BASE_SEED + 81)
+    w = torch.randn((K, N), generator=g, device="cuda") * 6e4
+    x = (torch.randn((M, K), generator=g, device="cuda") * 2.0 ** -12).to(torch.float16)
+    rec = B.quantize_layer(w) if kind == "w4" else B.quantize_layer_w8(w)
+    W = (B.dequantize_w4 if kind == "w4" else B.dequantize_w8)(*rec).double()
+    assert float(W.abs().max()) > 65504
+    fn, tag = (B.linear_w4a16, B.KIND_W4A16) if kind == "w4" else (B.linear_w8a16, B.KIND_W8A16)
+    y = fn(x, *rec, ws=B.new_workspace(B.workspace_bytes(tag, M, K, N))).double()
+    ref = x.double() @ W
+    assert bool(torch.isfinite(y).all()) and float((y - ref).norm() / ref.norm()) <= 2.0 ** -11
