@@ -66,7 +66,9 @@ enum { MORPH_GROUP_SIZE = 128 };
  * share a tile's K: need the workspace).  The library picks from the kind, the format and the shape.
  * workspace: morph_workspace_bytes(MORPH_KIND_FP16, M, K, N) bytes prepared once with
  * morph_workspace_init(); may be NULL when that size is 0.  One workspace must not be used by
- * two calls that can run concurrently (different streams).
+ * two calls that can run concurrently (different streams).  A smaller one (down to none) serves where it is
+ * enough for the kernels without the LDS ring: those then take the call, here and in morph_stack_forward, and
+ * the sums over K are rounded in another order.
  * Sizes: every array must be smaller than 4 GiB (32-bit byte offsets), else UNSUPPORTED. */
 int morph_linear_fp16(const void* x, const void* w, void* y, int M, int K, int N,
                       void* workspace, size_t workspace_bytes, void* stream);

@@ -165,3 +165,33 @@ def test_weights_beyond_the_fp16_range(B, kind):
     y = fn(x, *rec, ws=B.new_workspace(B.workspace_bytes(tag, M, K, N))).double()
     ref = x.double() @ W
     assert bool(torch.isfinite(y).all()) and float((y - ref).norm() / ref.norm()) <= 2.0 ** -11
+
+
+@pytest.mark.parametrize("kind,hidden,inter,M", [("fp16", 4096, 11008, 64), ("w8", 2048, 4096, 40), ("w8", 4096, 11008, 64)])
+def test_stack_on_the_workspace_of_the_older_kernels(B, kind, hidden, inter, M):
+    """A step through a stack takes a workspace that covers only what the kernels without the ring need, as a single linear does."""
+    tag = {"fp16": B.KIND_FP16, "w8": B.KIND_W8A16}[kind]
+    st = B.LayerStack(hidden, inter, M)
+    g = torch.Generator(device="cuda").manual_seed(synth.BASE_SEED + 83)
+    shapes = st._shapes()
+    layer = {}
+    for name, (K, N) in shapes.items():
+        w = torch.randn((K, N), generator=g, device="cuda") * 0.02
+        layer[name] = ("fp16", w.to(torch.float16)) if kind == "fp16" else ("w8",) + tuple(B.quantize_layer_w8(w))
+    st.add_layer(layer)
+    x = torch.randn((M, hidden), generator=g, device="cuda").to(torch.float16)
+    want = st.forward(x.clone())
+    B.set_tuning(B.TUNE_TILED, 1)
+    try:
+        need = max(B.workspace_bytes(tag, M, K, N) for K, N in shapes.values())
+        older = st.forward(x.clone())
+    finally:
+        B.set_tuning(B.TUNE_TILED, 0)
+    asked = max(B.workspace_bytes(tag, M, K, N) for K, N in shapes.values())
+    print(f"stack {kind} {hidden} {inter} M={M}: {need} and {asked} bytes", flush=True)
+    assert need < asked, "the ring needs no more here: another shape is wanted"
+    st.ws = B.new_workspace(need)
+    got = st.forward(x.clone())
+    # each of the linears ran on one of the two families; a step's own rounding is 2^-11 per linear (four, and four row steps)
+    for ref in (want, older):
+        assert float((got.double() - ref.double()).norm() / ref.double().norm()) <= 8 * 2.0 ** -11
