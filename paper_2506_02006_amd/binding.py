@@ -68,7 +68,7 @@ _lib = None
 # A decode linear is 5 to 20 us of device time and its marshalling through ctypes was about 10 us of host time,
 # so calls in a row ran at the host's pace (M = 1, 4096 x 4096, 4-bit: 10.5 us a call; 5.7 us now).  The functions below try the
 # C++ half first; it answers None when an argument is not as the call wants it or the library refuses, and the
-# Python path then runs the same checks and raises.
+# Python path then runs the same checks and raises.  A launch that failed raises MorphError there and then.
 _call = None
 _CALL_FNS = [
     "morph_linear_fp16", "morph_linear_w4a16", "morph_linear_w8a16", "morph_linear_w4a16_native",
@@ -88,6 +88,7 @@ def _load_call_path(L):
     mod = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(mod)
     mod.bind([ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _CALL_FNS])
+    mod.errors(MorphError)
     return mod
 
 

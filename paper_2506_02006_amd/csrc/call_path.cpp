@@ -6,8 +6,9 @@
 // host.  Here it is 1 us on top of the launch itself: M = 1, 4096 x 4096, 4-bit went from 10.5 to 5.7 us a call.
 //
 // Every function returns its result, or None when anything is not as the call wants it (type, device, shape,
-// contiguity, a status other than MORPH_OK: nothing was launched then); binding.py goes through its checked
-// path on None, which names what is wrong.
+// contiguity, or the library refuses it: nothing was launched then); binding.py goes through its checked
+// path on None, which names what is wrong.  MORPH_ERR_DEVICE is no refusal: something may have been launched, and the
+// error is the runtime's last, which asking has cleared.  It is raised here; a second call would run the work again and report success.
 #include <torch/csrc/autograd/python_variable.h>
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
@@ -22,7 +23,14 @@ using NativeFn = decltype(&morph_linear_w4a16_native);
 
 enum { F_DENSE = 0, F_W4, F_W8, F_NATIVE, F_DENSE_BF, F_W4_BF, F_W8_BF, F_NATIVE_BF, F_GLUE, F_GLUE_BF, F_COSINE, F_COSINE_BF,
        F_QUANT_W4, F_QUANT_W8, F_QUANT_NATIVE, F_DEQ_W4, F_DEQ_W8, F_DEQ_NATIVE, F_NATIVE_BYTES, F_COUNT };
+const char* const kName[F_COUNT] = {
+    "morph_linear_fp16", "morph_linear_w4a16", "morph_linear_w8a16", "morph_linear_w4a16_native",
+    "morph_linear_bf16", "morph_linear_w4a16_bf16", "morph_linear_w8a16_bf16", "morph_linear_w4a16_native_bf16",
+    "morph_glue", "morph_glue_bf16", "morph_cosine_rows", "morph_cosine_rows_bf16",
+    "morph_quantize_layer", "morph_quantize_layer_w8", "morph_quantize_layer_native_only",
+    "morph_dequantize_w4", "morph_dequantize_w8", "morph_dequantize_w4_native", "morph_w4_native_bytes"};
 void* g_fn[F_COUNT];
+PyObject* g_error;                                       // binding.MorphError
 constexpr int64_t kGroup = MORPH_GROUP_SIZE;
 constexpr int64_t kMaxInt = 0x7FFFFFFF;
 
@@ -44,6 +52,19 @@ inline PyObject* none()
 {
     PyErr_Clear();
     Py_RETURN_NONE;
+}
+
+// a status other than MORPH_OK: None after a refusal, the exception after a failure
+PyObject* refused(int rc, long which)
+{
+    if (rc != MORPH_ERR_DEVICE) return none();
+    PyErr_Clear();
+    if (!g_error) PyErr_Format(PyExc_RuntimeError, "%s: status %d", kName[which], rc);
+    else if (PyObject* e = PyObject_CallFunction(g_error, "is", rc, kName[which])) {
+        PyErr_SetObject(g_error, e);
+        Py_DECREF(e);
+    }
+    return nullptr;
 }
 
 // The C ABI runs without the interpreter's lock, as under ctypes: a launch that waits for room in a full queue
@@ -134,7 +155,7 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n)
         else
             rc = unlocked((QuantFn)g_fn[which], x->data_ptr(), (const int32_t*)w->data_ptr(), s->data_ptr(), (const int32_t*)z->data_ptr(), y->data_ptr(),
                                         (int)M, (int)K, (int)N, (int)group, wp, wb, stream_now());
-        if (rc != MORPH_OK) return none();
+        if (rc != MORPH_OK) return refused(rc, which);
         if (a[6] != Py_None) {
             Py_INCREF(a[6]);
             return a[6];
@@ -157,9 +178,10 @@ PyObject* glue(PyObject*, PyObject* const* v, Py_ssize_t n)
         const int64_t H = v[3] == Py_None ? a->size(1) / (op == MORPH_GLUE_QKV ? 3 : op == MORPH_GLUE_SWIGLU ? 2 : 1) : PyLong_AsLong(v[3]);
         if (M > kMaxInt || H < 0 || H > kMaxInt) return none();
         at::Tensor out = fresh({M, H}, dt, *a);
-        const int rc = unlocked((decltype(&morph_glue))g_fn[dt == at::kBFloat16 ? F_GLUE_BF : F_GLUE],
+        const int which = dt == at::kBFloat16 ? F_GLUE_BF : F_GLUE;
+        const int rc = unlocked((decltype(&morph_glue))g_fn[which],
             (int)op, a->data_ptr(), b ? b->data_ptr() : nullptr, out.data_ptr(), (int)M, (int)H, stream_now());
-        return rc == MORPH_OK ? THPVariable_Wrap(std::move(out)) : none();
+        return rc == MORPH_OK ? THPVariable_Wrap(std::move(out)) : refused(rc, which);
     });
 }
 
@@ -175,9 +197,10 @@ PyObject* cosine_rows(PyObject*, PyObject* const* v, Py_ssize_t n)
         const int64_t M = a->size(0), H = a->size(1);
         if (M > kMaxInt || H > kMaxInt) return none();
         at::Tensor cos = fresh({M}, at::kFloat, *a), mean = fresh({1}, at::kFloat, *a);
-        const int rc = unlocked((decltype(&morph_cosine_rows))g_fn[dt == at::kBFloat16 ? F_COSINE_BF : F_COSINE],
+        const int which = dt == at::kBFloat16 ? F_COSINE_BF : F_COSINE;
+        const int rc = unlocked((decltype(&morph_cosine_rows))g_fn[which],
             a->data_ptr(), b->data_ptr(), (float*)cos.data_ptr(), (float*)mean.data_ptr(), (int)M, (int)H, stream_now());
-        if (rc != MORPH_OK) return none();
+        if (rc != MORPH_OK) return refused(rc, which);
         PyObject* t = PyTuple_New(2);
         if (!t) return nullptr;
         PyTuple_SET_ITEM(t, 0, THPVariable_Wrap(std::move(cos)));
@@ -209,7 +232,7 @@ PyObject* quantize(PyObject*, PyObject* const* v, Py_ssize_t n)
             rc = unlocked((decltype(&morph_quantize_layer))g_fn[which], w->data_ptr(), code, (int32_t*)q.data_ptr(), s.data_ptr(), (int32_t*)z.data_ptr(),
                                                                 (int)K, (int)N, (int)group, stream_now());
         }
-        if (rc != MORPH_OK) return none();
+        if (rc != MORPH_OK) return refused(rc, which);
         PyObject* t = PyTuple_New(3);
         if (!t) return nullptr;
         PyTuple_SET_ITEM(t, 0, THPVariable_Wrap(std::move(q)));
@@ -238,7 +261,7 @@ PyObject* dequantize(PyObject*, PyObject* const* v, Py_ssize_t n)
         else
             rc = unlocked((decltype(&morph_dequantize_w4))g_fn[which], (const int32_t*)q->data_ptr(), s->data_ptr(), (const int32_t*)z->data_ptr(),
                                                                out.data_ptr(), (int)code, (int)K, (int)N, (int)group, stream_now());
-        return rc == MORPH_OK ? THPVariable_Wrap(std::move(out)) : none();
+        return rc == MORPH_OK ? THPVariable_Wrap(std::move(out)) : refused(rc, which);
     });
 }
 
@@ -261,8 +284,19 @@ PyObject* bind(PyObject*, PyObject* list)
     Py_RETURN_NONE;
 }
 
+// errors(cls): the exception that a failure raises, called with the status and the function's name
+PyObject* errors(PyObject*, PyObject* cls)
+{
+    Py_INCREF(cls);
+    PyObject* was = g_error;
+    g_error = cls;
+    Py_XDECREF(was);
+    Py_RETURN_NONE;
+}
+
 PyMethodDef kMethods[] = {
     {"bind", bind, METH_O, nullptr},
+    {"errors", errors, METH_O, nullptr},
     {"linear", (PyCFunction)(void*)linear, METH_FASTCALL, nullptr},
     {"glue", (PyCFunction)(void*)glue, METH_FASTCALL, nullptr},
     {"cosine_rows", (PyCFunction)(void*)cosine_rows, METH_FASTCALL, nullptr},
