@@ -97,6 +97,16 @@ void oracle_fp32_to_fp16(const float *f, uint16_t *h, int64_t n)
     for (int64_t i = 0; i < n; i++) h[i] = f2h(f[i]);
 }
 
+/* rint(v) clamped to -L .. L; 0 for NaN.  Clamped as a float: an int holds neither infinities nor what lies beyond 2^31. */
+static int rint_within(float v, int L)
+{
+    float t = rintf(v);
+    if (t != t) return 0;
+    if (t < (float)-L) return -L;
+    if (t > (float)L) return L;
+    return (int)t;
+}
+
 /* ---------- O1: quantize one weight matrix ---------- */
 /*
  * W      [K,N] fp32 row-major
@@ -132,12 +142,10 @@ int oracle_quantize_w4(const float *W, int K, int N, int G,
             if (s > 0x7BFFu) s = 0x7BFFu;                 /* saturate at 65504           */
             float sf = h2f(s);
             /* 3. zero point */
-            int z = (int)rintf(-lo / sf);
-            if (z < 0) z = 0;
-            if (z > 15) z = 15;
+            int z = rint_within(-lo / sf, 15);
             /* 4. codes: round the quotient first, then shift by the zero point */
             for (int k = k0; k < k1; k++) {
-                int q = (int)rintf(W[(size_t)k * N + n] / sf) + z;
+                int q = rint_within(W[(size_t)k * N + n] / sf, 15) + z;
                 if (q < 0) q = 0;
                 if (q > 15) q = 15;
                 /* 5. pack */
@@ -307,11 +315,9 @@ int oracle_quantize_w8(const float *W, int K, int N, int G,
             if (s < 0x0400u) s = 0x0400u;                 /* floor at 2^-14 */
             if (s > 0x7BFFu) s = 0x7BFFu;
             float sf = h2f(s);
-            int z = (int)rintf(-lo / sf);
-            if (z < 0) z = 0;
-            if (z > 255) z = 255;
+            int z = rint_within(-lo / sf, 255);
             for (int k = k0; k < k1; k++) {
-                int q = (int)rintf(W[(size_t)k * N + n] / sf) + z;
+                int q = rint_within(W[(size_t)k * N + n] / sf, 255) + z;
                 if (q < 0) q = 0;
                 if (q > 255) q = 255;
                 qweight[(size_t)k * NW + (n >> 2)] |= (uint32_t)q << (8 * (n & 3));

@@ -27,7 +27,9 @@ template <int BITS>
 __device__ __forceinline__ uint32_t code_divided(float v, float s, int z)
 {
     constexpr int L = (1 << BITS) - 1;
-    const int q = (int)rintf(__fdiv_rn(v, s)) + z;          // (infinities saturate, NaN converts to 0)
+    const float t = rintf(__fdiv_rn(v, s));
+    // clamped before it becomes an integer, which holds neither infinities nor quotients beyond 2^31 plus z (NaN: the code of 0)
+    const int q = (t == t ? (int)__builtin_amdgcn_fmed3f(t, -(float)L, (float)L) : 0) + z;
     return (uint32_t)(q < 0 ? 0 : (q > L ? L : q));
 }
 
@@ -126,8 +128,7 @@ __global__ __launch_bounds__(kQU * 16) void quantize_kernel(const WT* __restrict
         if (bits > 0x7BFFu) bits = 0x7BFFu;                 // at most 65504
         s = bit_cast<half_t>(bits);
         const float sf = (float)s;
-        zz = (int)rintf(__fdiv_rn(-l, sf));
-        zz = zz < 0 ? 0 : (zz > L ? L : zz);
+        zz = (int)__builtin_amdgcn_fmed3f(rintf(__fdiv_rn(-l, sf)), 0.0f, (float)L);
         sfl[tid] = sf;
         part[0][0][tid] = __fdiv_rn(1.0f, sf);              // only this thread reads and writes column tid here
         part[1][0][tid] = kMagic + (float)zz;

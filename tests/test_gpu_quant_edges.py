@@ -1,13 +1,15 @@
 """The quantizer and the dequantizer at the sizes and values where their kernels can go wrong, bit for bit against
 the oracle: widths around a unit of 8 columns and both workgroup widths (128 and 256 columns; the wide one from 512
-tiles of 128 x 256 on), and weights that sit exactly on, and a hair beside, the half steps between two codes, where
-the reciprocal multiply has to hand over to the division."""
+tiles of 128 x 256 on), weights that sit exactly on, and a hair beside, the half steps between two codes, where
+the reciprocal multiply has to hand over to the division, and infinities, NaN and weights that no scale reaches."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
 from paper_2506_02006_amd import synth
+
+from quant_formula import extreme_columns, formula_record
 
 pytestmark = pytest.mark.gpu
 
@@ -61,3 +63,22 @@ def test_quantize_dequantize_edges(B, oracle, bits, K, N, kind):
         assert torch.equal(ns, gs) and torch.equal(nz, gz)
         assert np.array_equal(B.dequantize_w4_native(nat, ns, nz, dtype=torch.float32).cpu().numpy(), want)
         assert np.array_equal(B.dequantize_w4_native(nat, ns, nz, dtype=torch.float16).cpu().numpy(), want.astype(np.float16))
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+def test_quantize_infinities_and_nan(B, oracle, bits, dtype):
+    """Columns whose range is infinite, or so wide that quotients pass 2^31, next to zero points of 1 and more: the codes of the format's formula."""
+    W = extreme_columns(256, 264)
+    d = torch.from_numpy(W).to(dtype).cuda()
+    W = d.float().cpu().numpy()
+    q, s, z = formula_record(W, (1 << bits) - 1)
+    print(f"extreme columns, {bits} bits, {dtype}", flush=True)
+    gq, gs, gz = (B.quantize_layer if bits == 4 else B.quantize_layer_w8)(d)
+    pw = 32 // bits
+    words = lambda c: (c.reshape(c.shape[0], -1, pw).astype(np.uint32) << (bits * np.arange(pw, dtype=np.uint32))).sum(2).astype(np.uint32)
+    assert np.array_equal(gs.cpu().numpy(), s)
+    assert np.array_equal(gz.cpu().numpy().view(np.uint32), words(z))
+    assert np.array_equal(gq.cpu().numpy().view(np.uint32), words(q))
+    if bits == 4:
+        assert np.array_equal(B.quantize_layer_native(d)[0].cpu().numpy(), oracle.repack_w4_native(words(q)))

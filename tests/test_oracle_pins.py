@@ -920,3 +920,16 @@ def test_p13_native_pins_catch_planted_mistakes(oracle):
     assert _native_pins_hold(*variant(), oracle.native_w4_bytes)                 # the faithful copy passes
     for slip in ("pe", "qr", "lane", "load", "blk", "re", "nib"):
         assert not _native_pins_hold(*variant(**{slip: True}), oracle.native_w4_bytes), slip
+
+
+@pytest.mark.parametrize("bits", [4, 8])
+def test_quantizers_at_the_ends_of_the_range(oracle, bits):
+    """O1 / O8 on infinities, NaN and quotients beyond 2^31: the formula's codes (numpy clamps before it converts)."""
+    from quant_formula import extreme_columns, formula_record
+    W = extreme_columns(256, 264)
+    q, s, z = formula_record(W, (1 << bits) - 1)
+    qw, sc, qz = (oracle.quantize_w4 if bits == 4 else oracle.quantize_w8)(W)
+    pw = 32 // bits
+    words = lambda c: (c.reshape(c.shape[0], -1, pw).astype(np.uint32) << (bits * np.arange(pw, dtype=np.uint32))).sum(2).astype(np.uint32)
+    assert np.array_equal(sc.view(np.float16), s)
+    assert np.array_equal(qz, words(z)) and np.array_equal(qw, words(q))
