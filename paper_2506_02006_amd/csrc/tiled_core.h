@@ -30,16 +30,17 @@ struct TiledTail {
 // compiler adds only makes those waits longer.
 // s_nop 4: a vector instruction that writes a scalar register and a memory instruction that reads it need five wait states between them.  The
 // compiler keeps them for its own loads and does not look in here, and it brings descriptor words and offsets that it has parked in vector lanes back with
-// v_readlane right before the block.  The five states also cover the one that m0 needs.
+// v_readlane right before the block.  The five states also cover the one that m0 needs.  m0, where the LDS address goes, is an operand,
+// so that the compiler writes it and knows what it holds (as a clobber it is a reserved register and draws a warning).
 template <bool NT>
 __device__ __forceinline__ void dma16(uint32_t lds, uint32_t voff, u32x4 rsrc, uint32_t soff)
 {
-    if constexpr (NT) asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-    else              asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    if constexpr (NT) asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    else              asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 __device__ __forceinline__ void dma4(uint32_t lds, uint32_t voff, u32x4 rsrc, uint32_t soff)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+    asm volatile("s_nop 4\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"{m0}"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
 // until at most N of this wave's loads are outstanding (they return in order)
 template <int N>

@@ -69,3 +69,24 @@ extern "C" __global__ void probe(const int* q, int* out)
     got = states_before_loads(lines)
     assert len(got) == 1 and got[0] is not None, (got, lines)
     assert got[0] >= 5, (got, [l for l in lines if "readlane" in l or "lds" in l or "nop" in l])
+
+
+def test_m0_is_known_to_be_written(tmp_path):
+    """A value that the compiler keeps in m0 does not outlive a load that writes m0: its own loads to one place, with one of ours between them."""
+    lines = assembly(tmp_path, """
+extern "C" __global__ void probe(const int* q, int* out, int to)
+{
+    __shared__ __align__(16) int buf[1024];
+    const __amdgpu_buffer_rsrc_t r = make_rsrc(q, 4096);
+    int* const at = buf + 256;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)at, 4, threadIdx.x * 4, 0, 0, 0);
+    dma4((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)buf, threadIdx.x * 4, rsrc_words(q, 4096), 0u);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)at, 4, threadIdx.x * 4, 256, 0, 0);
+    wait_vm<0>();
+    wg_barrier();
+    out[threadIdx.x] = buf[threadIdx.x + to];
+}
+""")
+    seen = [l for l in lines if is_lds_load(l) or re.match(r"s_\w+ m0,", l)]
+    assert sum(map(is_lds_load, seen)) == 3, seen
+    assert all(not is_lds_load(a) for a, b in zip(seen, seen[1:]) if is_lds_load(b)) and not is_lds_load(seen[0]), seen
