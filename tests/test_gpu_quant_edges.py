@@ -82,3 +82,21 @@ def test_quantize_infinities_and_nan(B, oracle, bits, dtype):
     assert np.array_equal(gq.cpu().numpy().view(np.uint32), words(q))
     if bits == 4:
         assert np.array_equal(B.quantize_layer_native(d)[0].cpu().numpy(), oracle.repack_w4_native(words(q)))
+
+
+@pytest.mark.parametrize("K,N", [(128, 8), (128, 136), (256, 248), (384, 264), (16384, 1032)])
+def test_both_orders_in_one_pass(B, oracle, K, N):
+    """morph_quantize_layer_native writes the canonical codes and the native ones; nothing beside either array."""
+    W = (np.random.default_rng([synth.BASE_SEED, 73, K, N]).standard_normal((K, N)) * 0.02).astype(np.float32)
+    print(f"both orders, K={K} N={N}", flush=True)
+    qw, sc, qz = oracle.quantize_w4(W)
+    d, guard = torch.from_numpy(W).cuda(), 4096
+    make = lambda n: torch.full((n + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    sizes = [B.w4_native_bytes(K, N), K * N // 2, K // 128 * N * 2, K // 128 * N // 2]
+    nat, can, s, z = bufs = [make(n) for n in sizes]
+    assert B.lib().morph_quantize_layer_native(d.data_ptr(), B.DTYPE_F32, nat.data_ptr(), s.data_ptr(), z.data_ptr(), can.data_ptr(), K, N, 128,
+                                               torch.cuda.current_stream().cuda_stream) == 0
+    for buf, n, want in zip(bufs, sizes, (oracle.repack_w4_native(qw), qw, sc, qz)):
+        got = buf.cpu().numpy()
+        assert np.array_equal(got[:n], np.ascontiguousarray(want).view(np.uint8).ravel())
+        assert (got[n:] == 0xA5).all()
