@@ -117,7 +117,7 @@ struct TiledPlan {
     double est_us;
 };
 TiledPlan plan_tiled(int q, int M, int K, int N, int bf);            // M > 64
-TiledPlan plan_tiled_few_rows(int q, int M, int K, int N);           // 17 .. 64, 8-bit and dense weights
+TiledPlan plan_tiled_few_rows(int q, int M, int K, int N, int bf);   // 17 .. 64, 8-bit and dense weights
 hipError_t launch_tiled(int q, const TiledArgs& a, hipStream_t st);  // q: 0 = dense, 1 = 4-bit, 2 = 8-bit codes
 
 // ---- prefill, M > 64 (prefill.hip) ----
