@@ -24,13 +24,12 @@ namespace morph {
 constexpr float kMagic = 12582912.0f;                     // 1.5 * 2^23, bit pattern 0x4B400000
 
 template <int BITS>
-__device__ __forceinline__ uint32_t code_divided(float v, float s, int z)
+__device__ __forceinline__ uint32_t code_divided(float v, float s, float z)
 {
-    constexpr int L = (1 << BITS) - 1;
+    constexpr float L = (float)((1 << BITS) - 1);
     const float t = rintf(__fdiv_rn(v, s));
-    // clamped before it becomes an integer, which holds neither infinities nor quotients beyond 2^31 plus z (NaN: the code of 0)
-    const int q = (t == t ? (int)__builtin_amdgcn_fmed3f(t, -(float)L, (float)L) : 0) + z;
-    return (uint32_t)(q < 0 ? 0 : (q > L ? L : q));
+    // in floating point to the end: an integer holds neither infinities nor quotients beyond 2^31 plus z (t + z is exact where it matters; NaN: the code of 0)
+    return (uint32_t)__builtin_amdgcn_fmed3f(t == t ? t + z : z, 0.0f, L);
 }
 
 // the 8 columns of a row, widened
@@ -174,7 +173,7 @@ __global__ __launch_bounds__(kQU * 16) void quantize_kernel(const WT* __restrict
             for (int k = 0; k < WPU; k++) word[i][k] = 0;
 #pragma unroll
             for (int j = 0; j < 8; j++)
-                word[i][j / CPW] |= code_divided<BITS>(v[i].at(j), sfl[8 * u + j], (int)(m[j] - kMagic)) << (BITS * (j % CPW));
+                word[i][j / CPW] |= code_divided<BITS>(v[i].at(j), sfl[8 * u + j], m[j] - kMagic) << (BITS * (j % CPW));
         }
     }
     if (qweight && live) {
