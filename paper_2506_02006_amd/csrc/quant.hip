@@ -15,10 +15,10 @@ namespace morph {
 // The code of a weight is rint(v / s) + z clamped to 0 .. L, the division correctly rounded.  Without dividing:
 // with r = 1 / s and m = 1.5 * 2^23 + z, f = fma(v, r, m) holds rint(v r) + z in its low mantissa bits (the unit of
 // f is 1), so clamping f to [1.5 * 2^23, + L] leaves the code there, and Sum (bits of f << BITS * j) over the codes of
-// a word is the packed word plus a constant.  v r lies within 2^-23 |v r| of the rounded quotient, so both round to
-// the same integer unless v r is within that of a half-integer; |v r| beyond 2 L is clamped whatever it rounds to, so
-// the distance to watch for is 2 L * 2^-23 (kNear has twice that).  d = v r - rint(v r) tells, and the words in which some
-// lane comes that close (one in a hundred per wave, or one in fifteen with 8 bits) are worked out by dividing, as is NaN.
+// a word is the packed word plus a constant.  r and the rounded quotient are each off by at most 2^-24 of themselves, so v r lies
+// within 2^-23 |v / s| of the rounded quotient and both round to the same integer unless v r is within that of a half-integer; beyond
+// |v / s| = L either gives the same code, so the distance to watch for is L * 2^-23 (kNear has twice that).  d = v r - rint(v r) tells, and the words in
+// which some lane comes that close (one in 270 per wave, or one in 16 with 8 bits) are worked out by dividing, as is NaN.
 // Measured (4096 x 22016, cold): bfloat16 source -> 4-bit record 63.8 -> 48.8 us, fp32 95.1 -> 77.3 (5.3 TB/s); straight into the native order
 // instead of by way of the canonical record 96.5 -> 49.0 us.
 constexpr float kMagic = 12582912.0f;                     // 1.5 * 2^23, bit pattern 0x4B400000
@@ -68,13 +68,17 @@ __global__ __launch_bounds__(kQU * 16) void quantize_kernel(const WT* __restrict
     constexpr int   L = (1 << BITS) - 1;                    // largest code
     constexpr int   CPW = 32 / BITS, WPU = 8 / CPW;         // codes per word, words per unit of 8 columns
     constexpr int   kQC = 8 * kQU, kThreads = 16 * kQU, kWaves = kThreads / 64;
-    constexpr float kNear = 0.5f - 4.0f * (float)L * 0x1p-23f;
+    constexpr float kNear = 0.5f - 2.0f * (float)L * 0x1p-23f;
     __shared__ __align__(16) float part[2][kWaves][kQC];    // -> column ranges; then [0][0]: 1 / s, [1][0]: 1.5 * 2^23 + z
     __shared__ float sfl[kQC];
     const int tid = threadIdx.x, wave = tid >> 6;
     const int u = tid & (kQU - 1), oct = tid / kQU;
     const int NW = N / CPW;
-    const int n0 = blockIdx.x * kQC, n = n0 + 8 * u;
+    // Workgroup L runs on XCD L % 8.  Where the number of column tiles is a power of two, an XCD would see the same few columns of every group, and with
+    // the rows' pitch a power of two the same channels of its L2: the tiles of a group move on by one from group to group there (fp32, 4096 x 4096
+    // 21.6 -> 16.4 us, 14336 x 4096 60.4 -> 50.2; elsewhere it would cost the division by an odd number, 1 %).
+    const int bx = (gridDim.x & (gridDim.x - 1)) == 0 ? (int)((blockIdx.x + blockIdx.y) & (gridDim.x - 1)) : (int)blockIdx.x;
+    const int n0 = bx * kQC, n = n0 + 8 * u;
     const int g  = blockIdx.y;
     const bool live = n < N;
     const size_t row0 = (size_t)g * kGroup + 8 * oct;
