@@ -162,7 +162,8 @@ hipError_t launch_probe_read(const void* src, size_t bytes, void* out, hipStream
 hipError_t launch_probe_mfma(int iters, void* out, hipStream_t st);
 
 // tuning knobs (morph_set_tuning).  14: the tile of the LDS-ring kernels beyond 64 rows, 16 x (layout + 1) + 16-row tiles of a wave (1: those kernels stay
-// out, whatever the rows); 15: the most workgroups that share a unit's K there.
+// out, whatever the rows, but for canonical 4-bit codes with fp16 rows at 17 .. 64, which no other register-tiled kernel reads: key 12 = 2 or 3 sends those to
+// the general streaming kernels); 15: the most workgroups that share a unit's K there.
 int  tuning_get(int key);
 void tuning_set(int key, int value);
 enum { TUNE_DECODE_SPLIT = 0, TUNE_DECODE_WGS = 1, TUNE_PREFILL_TILE = 2, TUNE_DECODE_WAVES = 3, TUNE_PREFILL_SPLIT = 4, TUNE_PREFILL_MAP = 5, TUNE_DECODE_MAX_M = 6, TUNE_DECODE_SLICE = 7, TUNE_DECODE_STREAM = 8, TUNE_DECODE_SCATTER = 9, TUNE_PREFILL_GRID = 10, TUNE_PREFILL_STAGING = 11, TUNE_SMALL = 12, TUNE_SMALL_DEPTH = 13, TUNE_TILED = 14, TUNE_TILED_SPLIT = 15, TUNE_COUNT = 16 };
