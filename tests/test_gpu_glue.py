@@ -10,6 +10,18 @@ pytestmark = pytest.mark.gpu
 
 TOL = {"fp16": 2e-3, "bf16": 8e-3}      # of the largest value of a step: one rounding of the result, 2^-12 (2^-9), of values up to about 5 rms, and a margin of 4
 
+# element by element: the rounding of the result and 2e-5 for fp32 (the exponential at 88: 127 x 2^-24 of its argument in powers of two); half the
+# smallest fp16 number, the smallest normal bfloat16 one
+REL = {"fp16": 2.0 ** -11 + 2e-5, "bf16": 2.0 ** -8 + 2e-5}
+TINY = {"fp16": 2.0 ** -25, "bf16": 2.0 ** -126}
+
+
+def swiglu_fp32(gu, H):
+    """The step by its definition: fp32 up to the products, the row's mean square in 64 bits."""
+    x, u = gu[:, :H].float(), gu[:, H:].float()
+    h = (x / (1.0 + torch.exp(-x)) * u).double()
+    return (h / torch.sqrt((h * h).mean(dim=1, keepdim=True) + 1e-6)).numpy()
+
 
 @pytest.fixture(scope="module")
 def B():
@@ -35,18 +47,31 @@ def test_glue_at_the_edges_of_the_vectors_per_thread(B, oracle, H, fmt):
 
 @pytest.mark.parametrize("fmt", ["fp16", "bf16"])
 def test_swiglu_on_gates_that_overflow_the_exponential(B, fmt):
-    """One special gate per row: finite ones far out on either side leave the row as the definition has it; what is infinite or NaN by
-    the definition (silu(inf) = inf, silu(-inf) = NaN) is so here, and only where it is there."""
+    """One special gate per row: finite ones far out on either side leave every column as the definition has it (in fp32, where the
+    exponential overflows beyond 88.72), the special one among them; what is infinite or NaN by the definition (silu(inf) = inf,
+    silu(-inf) = NaN) is so here, and only where it is there."""
     H, dt = 4104, torch.float16 if fmt == "fp16" else torch.bfloat16
-    gates = [-88.0, -89.0, -104.0, -60000.0, 60000.0, float("inf"), float("-inf"), float("nan")]
+    gates = [-87.0, -87.5, -88.0, -88.5, -89.0, -104.0, -60000.0, 60000.0, float("inf"), float("-inf"), float("nan")]
     g = torch.Generator().manual_seed(7)
     gu = torch.randn((len(gates), 2 * H), generator=g).to(dt)
     for i, v in enumerate(gates):
-        gu[i, 100] = v
-    x, u = gu[:, :H].float(), gu[:, H:].float()
-    h = x / (1.0 + torch.exp(-x)) * u                    # fp32, as the step's definition goes
-    want = (h * (1.0 / torch.sqrt((h * h).mean(dim=1, keepdim=True) + 1e-6))).double().numpy()
+        gu[i, 100], gu[i, H + 100] = v, 1.0
+    want = swiglu_fp32(gu, H)
     got = B.glue(B.GLUE_SWIGLU, gu.cuda()).double().cpu().numpy()
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
-    for i in range(5):
-        assert np.abs(got[i] - want[i]).max() <= TOL[fmt] * np.abs(want[i]).max(), gates[i]
+    for i in range(8):
+        assert (np.abs(got[i] - want[i]) <= REL[fmt] * np.abs(want[i]) + TINY[fmt]).all(), gates[i]
+
+
+def test_swiglu_gates_whose_reciprocal_is_subnormal(B):
+    """1 / (1 + exp(-x)) is below the smallest normal number for gates under -87.3; against up values of 10^36 the quotient is what
+    the row is made of."""
+    H = 4104
+    gates = [-87.0, -87.5, -88.0, -88.5]
+    gu = torch.zeros((len(gates), 2 * H), dtype=torch.bfloat16)
+    for i, v in enumerate(gates):
+        gu[i, 100], gu[i, H + 100] = v, 2.0 ** 120
+    want = swiglu_fp32(gu, H)
+    assert (np.abs(want[:, 100]) > 60.0).all()
+    got = B.glue(B.GLUE_SWIGLU, gu.cuda()).double().cpu().numpy()
+    assert (np.abs(got - want) <= REL["bf16"] * np.abs(want)).all()
