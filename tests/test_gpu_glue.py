@@ -32,11 +32,12 @@ def B():
 
 
 @pytest.mark.parametrize("fmt", ["fp16", "bf16"])
-@pytest.mark.parametrize("H", [8, 4096, 4104, 8192, 8200, 12288, 12296, 16384, 16392, 40008])
-def test_glue_at_the_edges_of_the_vectors_per_thread(B, oracle, H, fmt):
+@pytest.mark.parametrize("M,H", [(3, H) for H in (8, 4096, 4104, 8192, 8200, 12288, 12296, 16384, 16392, 40008)] + [(M, H) for M in (256, 257) for H in (8, 4104, 8200, 16392)])
+def test_glue_at_the_edges_of_the_vectors_per_thread(B, oracle, M, H, fmt):
+    """... for a few rows and for about as many as there are compute units."""
     rng = np.random.default_rng([synth.BASE_SEED, 600, H])
     dt = torch.float16 if fmt == "fp16" else torch.bfloat16
-    dev = lambda cols, s: torch.from_numpy((rng.standard_normal((3, cols)) * s).astype(np.float32)).to(dt).cuda()
+    dev = lambda cols, s: torch.from_numpy((rng.standard_normal((M, cols)) * s).astype(np.float32)).to(dt).cuda()
     f64 = lambda t: t.double().cpu().numpy()
     qkv, a, b, gu = dev(3 * H, 2.0), dev(H, 1.0), dev(H, 3.0), dev(2 * H, 2.0)
     for op, p, q, want in ((B.GLUE_QKV, qkv, None, oracle.glue_qkv(f64(qkv))), (B.GLUE_RESIDUAL, a, b, oracle.glue_residual(f64(a), f64(b))),
@@ -46,16 +47,17 @@ def test_glue_at_the_edges_of_the_vectors_per_thread(B, oracle, H, fmt):
 
 
 @pytest.mark.parametrize("fmt", ["fp16", "bf16"])
-def test_swiglu_on_gates_that_overflow_the_exponential(B, fmt):
+@pytest.mark.parametrize("H,col", [(4104, 100), (4104, 4100), (16392, 100), (16392, 16390), (20488, 16390)])
+def test_swiglu_on_gates_that_overflow_the_exponential(B, fmt, H, col):
     """One special gate per row: finite ones far out on either side leave every column as the definition has it (in fp32, where the
     exponential overflows beyond 88.72), the special one among them; what is infinite or NaN by the definition (silu(inf) = inf,
-    silu(-inf) = NaN) is so here, and only where it is there."""
-    H, dt = 4104, torch.float16 if fmt == "fp16" else torch.bfloat16
+    silu(-inf) = NaN) is so here, and only where it is there.  The special column is in a thread's first vector, in its last, and in one that is read twice."""
+    dt = torch.float16 if fmt == "fp16" else torch.bfloat16
     gates = [-87.0, -87.5, -88.0, -88.5, -89.0, -104.0, -60000.0, 60000.0, float("inf"), float("-inf"), float("nan")]
     g = torch.Generator().manual_seed(7)
     gu = torch.randn((len(gates), 2 * H), generator=g).to(dt)
     for i, v in enumerate(gates):
-        gu[i, 100], gu[i, H + 100] = v, 1.0
+        gu[i, col], gu[i, H + col] = v, 1.0
     want = swiglu_fp32(gu, H)
     got = B.glue(B.GLUE_SWIGLU, gu.cuda()).double().cpu().numpy()
     assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want))
