@@ -65,6 +65,19 @@ def test_swiglu_on_gates_that_overflow_the_exponential(B, fmt, H, col):
         assert (np.abs(got[i] - want[i]) <= REL[fmt] * np.abs(want[i]) + TINY[fmt]).all(), gates[i]
 
 
+@pytest.mark.parametrize("fmt", ["fp16", "bf16"])
+def test_swiglu_of_every_gate(B, fmt):
+    """All finite values of the format, each in a row of its own kind: the short quotient has to serve them from -87 up, the division below."""
+    dt = torch.float16 if fmt == "fp16" else torch.bfloat16
+    x = torch.arange(65536, dtype=torch.int32).to(torch.int16).view(dt)
+    x = x[torch.isfinite(x) & (x.abs() < 60000.0)].sort().values          # rows of gates of like size, so that no row hides its small ones
+    H = 64
+    x = x[:x.numel() // H * H].view(-1, H)
+    gu = torch.cat([x, torch.ones_like(x)], 1)
+    want, got = swiglu_fp32(gu, H), B.glue(B.GLUE_SWIGLU, gu.cuda()).double().cpu().numpy()
+    assert (np.abs(got - want) <= REL[fmt] * np.abs(want) + TINY[fmt]).all()
+
+
 def test_swiglu_gates_whose_reciprocal_is_subnormal(B):
     """1 / (1 + exp(-x)) is below the smallest normal number for gates under -87.3; against up values of 10^36 the quotient is what
     the row is made of."""
