@@ -5,9 +5,10 @@
 //   * a short head: the division of K over workgroups and waves is prepared on the host, and a wave
 //     reaches its first load after a few dozen instructions;
 //   * loads that run three k-steps (of 32 rows) ahead of their use through a ring of four register
-//     stages in a loop unrolled by four (= one quantization group); a wave takes whole groups, so
-//     the only loads that fall outside its range are the last three slots' (pushed past the buffer,
-//     they return zeros without memory traffic) and the compiler's wait counts are exact;
+//     stages in a loop unrolled by four (= one quantization group); a wave takes whole groups (dense
+//     weights: see dense_by_steps), so the only loads that fall outside its range are the last three
+//     slots' (pushed past the buffer, they return zeros without memory traffic) and the compiler's
+//     wait counts are exact;
 //   * results in registers until the k loop is over, and no reload from scratch memory inside the
 //     loop (such a reload waits for every load in flight, which undoes the prefetch);
 //   * a hand-over between the workgroups that split K which stays inside one XCD's L2 (see
@@ -74,7 +75,7 @@ struct SmallTail {
 // What a workgroup needs to find its place travels as leading scalar kernel arguments (fourteen dwords with the
 // pointers: as many as are in registers when a wave starts); a field of the structure above costs a trip to
 // memory before the first load could be issued.  Packed two to a dword:
-//   ms = M | S << 16;  qr = groups per split | (splits that take one more) << 16 (dense: k-steps per split | (...) << 28);
+//   ms = M | S << 16;  qr = groups per split | (splits that take one more) << 16 (dense: k-steps or groups per split | (...) << 28);
 //   tiles_sl = column tiles of 256 | sl_shift << 16 (0: one slice of rows; 1: two slices of 32 rows, workgroups
 //   (tile, slice, split));  inv_s = ceil(65536 / S): j / S = (j * inv_s) >> 16 for the j that occur.
 
@@ -1240,20 +1241,20 @@ __global__ __launch_bounds__(kWideWaves * 64) void decode_wide_kernel(
 // wants 8 consecutive k of one column), and the accumulators are the running results.  MT: tiles of 16
 // rows per slice (1: M <= 16).  A k-step is 8 KB per wave, three of them in flight.
 // Bound: memory, in pieces of 512 bytes of a row (a read of the same pieces by as many workgroups and nothing else: 4096 x 12288 17.4 us,
-// 4096 x 22016 33.0, 11008 x 4096 15.9), the start and the hand-over.  K is shared out in k-steps: in runs of 128 rows, as the
-// quantized kernels share it out, the slowest wave had up to a quarter more to walk than the average (7 / 32 rows, us: 11008 x 4096
-// 18.34 / 20.74 -> 17.35 / 19.51, 4096 x 12288 19.59 / 23.03 -> 19.17 / 22.49; 4096 x 22016 and 4096 x 4096, even before, unchanged).
+// 4096 x 22016 33.0, 11008 x 4096 15.9), the start and the hand-over.
+// STEPS: K is shared out in k-steps instead of the runs of 128 rows that the quantized kernels walk; up to three steps are left after the last round of four
+// (dense_by_steps says where).
 // ------------------------------------------------------------------------------------------------
 struct DenseStage {
     u32x4 r[8];                                  // row 8 b + i of the k-step: the lane's 8 columns
 };
 
-template <int MT, bool BF>
+template <int MT, bool BF, bool STEPS>
 __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     const uint32_t* w, const void* x_all, const void*, const uint32_t*, int K, int N, int ms, int qr,
     int tiles_sl, int inv_s, SmallTail t)
 {
-    const int M_all = ms & 0xFFFF, S = ms >> 16, q_steps = qr & 0x0FFFFFFF, r_steps = (int)((uint32_t)qr >> 28);
+    const int M_all = ms & 0xFFFF, S = ms >> 16, q_units = qr & 0x0FFFFFFF, r_units = (int)((uint32_t)qr >> 28);
     // as in decode_mid_kernel: per wave two buffers of x (16 MT rows of 128 k, pieces XOR-swizzled by the row),
     // afterwards the results of one tile of 16 rows at a time
     __shared__ __align__(16) u32x4 sm[kSmWaves * 1024];
@@ -1308,12 +1309,12 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
         }
     };
     auto begin_pass = [&](int split) {
-        // k-steps of the split, then of this wave's half.  Nothing ties a dense wave to the groups of 128 the quantized kernels
-        // walk: with whole groups a fifth of K = 4096 left one half of the waves 16 steps where 12.8 are the average.
-        const int kb = split * q_steps + (split < r_steps ? split : r_steps);
-        const int nk = q_steps + (split < r_steps ? 1 : 0);
-        ks0 = kb + ((kh * nk) >> 1);
-        ks1 = kb + (((kh + 1) * nk) >> 1);
+        // k-steps, or runs of four, of the split, then of this wave's half
+        constexpr int U = STEPS ? 1 : kRing;
+        const int kb = split * q_units + (split < r_units ? split : r_units);
+        const int nk = q_units + (split < r_units ? 1 : 0);
+        ks0 = U * (kb + ((kh * nk) >> 1));
+        ks1 = U * (kb + (((kh + 1) * nk) >> 1));
         load_xgroup(ks0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1365,7 +1366,7 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
         };
         store_xgroup(0);
         int ks = ks0;                                    // rounds of four steps = 128 k of x
-        for (; ks + kRing <= ks1; ks += kRing) {
+        for (; STEPS ? ks + kRing <= ks1 : ks < ks1; ks += kRing) {
 #pragma unroll
             for (int u = 0; u < kRing; u++) {
                 load_stage(st[(u + kAhead) % kRing], ks + u + kAhead);
@@ -1377,10 +1378,11 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
             store_xgroup(xb ^ 1);                        // the next round's x, requested at the top of this one
             xb ^= 1;
         }
-        // up to three more steps: they were requested by the last round (or by begin_pass)
-        if (ks < ks1) multiply(st[0], 0);
-        if (ks + 1 < ks1) multiply(st[1], 1);
-        if (ks + 2 < ks1) multiply(st[2], 2);
+        if constexpr (STEPS) {                           // up to three more: they were requested by the last round (or by begin_pass)
+            if (ks < ks1) multiply(st[0], 0);
+            if (ks + 1 < ks1) multiply(st[1], 1);
+            if (ks + 2 < ks1) multiply(st[2], 2);
+        }
         // one tile of 16 rows at a time through LDS, summed over the two halves of K
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) {
@@ -1399,17 +1401,32 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     finish_over_splits(t, S, p, nvec, base, &fresh_word, run_pass, begin_pass, vec_store_y);
 }
 
-template <class Kernel>
-hipError_t launch_small_with(Kernel kernel, int waves, const SmallArgs& a, hipStream_t st)
+// Whether dense weights are shared out in k-steps instead of runs of 128 rows, of which the slowest half of a workgroup's waves has up to three steps more
+// to walk: us, runs / steps, 11008 x 4096 at 7 rows (12 / 11 steps) 19.25 / 18.3, at 32 rows 21.4 / 20.3, 4096 x 12288 at 7 rows (16 / 13) 20.7 / 20.3, 2048 x 5120 at
+// 64 rows (8 / 7) 14.3 / 13.0, and where only the average half is shorter, at 16 rows 9.05 / 8.65.  Not where
+//   - the runs come out even: the code for left-over steps costs 0.03 to 0.2 us whether there are any or not (64 rows: 4096 x 3072 13.3 / 13.6, 6144 x 4096 17.1 / 17.4);
+//   - beyond 32 rows a half has 16 steps and more, which gains nothing (11008 x 4096 at 40 rows, 24 / 22: 26.4 / 27.6; 7040 x 5120, 24 / 22: 29.3 / 30.0;
+//     9088 x 3640, 20 / 18: 27.3 / 27.2);
+//   - up to 32 rows a part is one run and the workgroups fill the chip, so that one half may as well have nothing (1024 x 8192 at 7 rows 6.97 / 7.1; 1024 x 4096,
+//     half as many workgroups, 6.1 / 6.0; 2048 x 2048 at 64 rows 8.8 / 8.3).
+bool dense_by_steps(int M, int K, int S, int tiles)
 {
-    const int G = a.K / kGroup, T = a.K / 32;
+    const int T = K / 32, most = (T + S - 1) / S;
+    if (T % S == 0 && most % 8 == 0) return false;
+    return M > 32 ? (most + 1) / 2 < 16 : T != 4 * S || tiles * S <= 160;
+}
+
+template <class Kernel>
+hipError_t launch_small_with(Kernel kernel, int waves, const SmallArgs& a, hipStream_t st, bool by_steps = false)
+{
+    const int q = a.K / (by_steps ? 32 : kGroup) / a.S, r = a.K / (by_steps ? 32 : kGroup) % a.S;
     SmallTail t;
     t.y = a.y; t.slots = a.slots; t.ctl = a.ctl; t.polls = a.polls; t.nb = (a.M + 3) / 4;
     t.far = a.far;
     const int sl_shift = a.M > 32 ? 1 : 0;
     const int grid = 8 * ((a.tiles + 7) / 8) * a.S << sl_shift;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * 64), 0, st,
-                       (const uint32_t*)a.w, a.x, a.scales, (const uint32_t*)a.qzeros, a.K, a.N, a.M | (a.S << 16), a.dense ? (T / a.S) | ((T % a.S) << 28) : (G / a.S) | ((G % a.S) << 16),
+                       (const uint32_t*)a.w, a.x, a.scales, (const uint32_t*)a.qzeros, a.K, a.N, a.M | (a.S << 16), q | (int)((uint32_t)r << (a.dense ? 28 : 16)),
                        a.tiles | (sl_shift << 16), (65536 + a.S - 1) / a.S, t);
     return hipGetLastError();
 }
@@ -1422,8 +1439,9 @@ hipError_t launch_small_m(const SmallArgs& a, hipStream_t st)
         return launch_small_with(decode_small8_kernel<4, BF>, kSmWaves, a, st);
     }
     if (a.dense) {
-        if (a.M <= 16) return launch_small_with(decode_dense_kernel<1, BF>, kSmWaves, a, st);
-        return launch_small_with(decode_dense_kernel<2, BF>, kSmWaves, a, st);
+        if (dense_by_steps(a.M, a.K, a.S, a.tiles))
+            return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, true>, kSmWaves, a, st, true) : launch_small_with(decode_dense_kernel<2, BF, true>, kSmWaves, a, st, true);
+        return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, false>, kSmWaves, a, st) : launch_small_with(decode_dense_kernel<2, BF, false>, kSmWaves, a, st);
     }
     if (a.native) {
         if (a.wide && a.M <= 4)  return launch_small_with(decode_wide_kernel<1, 1, BF>, kWideWaves, a, st);
