@@ -401,11 +401,20 @@ static DecodePlan plan_small(int q, int M, int K, int N, int native)
         // 1024 x 4096 6.91 -> 6.01, 3072 x 3072 8.20 -> 7.84); where eight would leave one workgroup, one it stays (no workspace needed).
         S = split_for(halves > 1 ? T / 4 : 1);
         // Splits that all start a multiple of 1 MB apart read the same channels at the same time.  One fewer makes their parts uneven; at 128
-        // k-steps and fewer three fewer, as the hand-over over sixteen splits is a larger part there.  7 rows, us: 4096 x 4096 16 splits 11.0, 15 10.1,
-        // 13 9.35; 4096 x 2048 8.8, 8.1, 7.9; 2048 x 4096 7.6, 7.35, 6.8; 8192 x 2048 11.9, 10.85, 11.2; 6144 x 4096 11.7, 11.6, 11.4;
-        // 14336 x 4096 21.3, 20.4, 21.0.  512 KB do not show (4096 x 1024 7.3, 7.3, 7.6; 2048 x 2048 6.0, 5.95, 5.9), nor odd multiples of it
-        // (11008 x 4096 16.7, 16.9, 17.3).  Below twelve splits one fewer costs more (5120 x 5120 10 splits 13.95, 9 14.2; 1024 x 4096 8 splits 6.0, 7 6.2).
-        if (S >= 12 && T % S == 0 && (long long)(T / S) * N * 64 % (1 << 20) == 0 && tuning_get(TUNE_DECODE_SPLIT) <= 0) S -= T <= 128 ? 3 : 1;
+        // k-steps and fewer three fewer, as the hand-over over many splits is a larger part there.  us at 7 / 32 rows, even splits -> fewer: 4096 x 4096 16 splits
+        // 10.6 / 13.0, 13 9.6 / 12.1; 2048 x 4096 7.3 / 9.4, 6.9 / 9.1; 1536 .. 1920 x 4096 12 .. 15 splits 6.6 .. 7.0 / 8.7 .. 9.2, 9 .. 12 6.4 .. 6.7 / 8.4 .. 8.8;
+        // 4096 x 2048 8.9 / 10.8, 7.9 / 10.1 (64 rows 11.8, 10.5); 8192 x 2048 16 splits 11.2 / 13.35, 15 10.8 / 13.35 (64 rows 14.7, 13.8); 8192 x 1024 10.3, 9.95
+        // (32 rows 12.35, 12.55: fewer than 128 workgroups); 8192 x 4096 15.4 / 17.7, 14.7 / 17.3; 14336 x 4096 23.3 / 25.6, 22.7 / 25.0.
+        //   A workgroup's part grows by a sixteenth with it.  Beyond 16 k-steps to a part, and at multiples of 1 MB that are no power of two, that costs more
+        // (12288 x 2048 14.0 / 16.4, 14.2 / 17.4; 16384 x 1024 15.3 / 17.9, 15.7 / 19.1; 8192 x 3072 13.4 / 15.65, 13.3 / 16.0), but where the workgroups of 4096 columns take
+        // every compute unit and memory is the bound whatever the part.  512 KB do not show (4096 x 1024 7.3, 15 splits 7.3; 2048 x 2048 6.0, 5.95), nor odd multiples of
+        // them (11008 x 4096 16.7, 16.9).  Below twelve splits one fewer costs more (5120 x 5120 10 splits 13.95, 9 14.2; 1024 x 4096 8 splits 6.0, 7 6.2).
+        const long long apart = (long long)(T / S) * N * 64;
+        if (S >= 12 && T % S == 0 && apart % (1 << 20) == 0 && tuning_get(TUNE_DECODE_SPLIT) <= 0) {
+            const bool takes_all = pl.tiles * S >= target;
+            const bool short_part = T / S <= 16 && (apart & (apart - 1)) == 0 && (M <= 16 || pl.tiles * slices * S >= 128);
+            if (takes_all || short_part) S -= T <= 128 ? 3 : 1;
+        }
     } else {
         S = split_for((M <= 16 && q != 0) ? T / 4 : halves);
     }

@@ -307,3 +307,17 @@ def test_decode_layout_fits_the_device_at_once(L):
                         assert tiles * S * slices <= 256, (kind, M, K, N, list(plan))
                         assert ((tiles + 7) // 8) * S * slices <= 32, (kind, M, K, N, list(plan))
     assert seen > 3000
+
+
+@pytest.mark.parametrize("M,K,N,S", [
+    (7, 128, 264, 1), (7, 384, 264, 1), (7, 512, 264, 4), (7, 1024, 4096, 8), (64, 2048, 2048, 16), (7, 11008, 4096, 16),      # four k-steps to a workgroup
+    (7, 4096, 4096, 13), (32, 4096, 4096, 13), (64, 4096, 2048, 13), (1, 2048, 4096, 13), (7, 1536, 4096, 9), (32, 1920, 4096, 12),
+    (7, 8192, 4096, 15), (32, 14336, 4096, 15), (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15),
+    (32, 8192, 1024, 16), (1, 12288, 2048, 16), (32, 12288, 2048, 16), (64, 12288, 2048, 16), (7, 16384, 1024, 16), (32, 8192, 3072, 16),   # a longer part costs more
+    (7, 4096, 1024, 16), (7, 5120, 4096, 16), (7, 5120, 5120, 10)])                                                               # half megabytes do not show
+def test_dense_splits(L, M, K, N, S):
+    """How many workgroups share K of a dense linear: uneven splits where even ones would start whole megabytes apart and the workgroups' parts are short or the
+    chip is full, even ones elsewhere."""
+    plan = (ctypes.c_int * 5)()
+    assert L.morph_plan_decode(0, M, K, N, plan) == 0
+    assert plan[0] == 1 and plan[2] == S, list(plan)
