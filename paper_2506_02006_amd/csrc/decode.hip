@@ -415,6 +415,10 @@ static DecodePlan plan_small(int q, int M, int K, int N, int native)
             const bool short_part = T / S <= 16 && (apart & (apart - 1)) == 0 && (M <= 16 || pl.tiles * slices * S >= 128);
             if (takes_all || short_part) S -= T <= 128 ? 3 : 1;
         }
+        // The sum over up to four splits is read four wide, over more sixteen wide (finish_over_splits), which shows beyond 16 rows: four instead of five where the
+        // slowest half of the waves has no more to walk then (us, 5 -> 4: 768 x 6144 at 33 rows 9.2 -> 8.6, 1024 x 12288 at 32 11.8 -> 10.95; at 1 row 8.17, 8.15).
+        auto slowest = [&](int s) { return ((T + s - 1) / s + 1) / 2; };
+        if (S == 5 && M > 16 && slowest(4) == slowest(5) && tuning_get(TUNE_DECODE_SPLIT) <= 0) S = 4;
     } else {
         S = split_for((M <= 16 && q != 0) ? T / 4 : halves);
     }

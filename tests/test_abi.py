@@ -314,6 +314,7 @@ def test_decode_layout_fits_the_device_at_once(L):
     (7, 4096, 4096, 13), (32, 4096, 4096, 13), (64, 4096, 2048, 13), (1, 2048, 4096, 13), (7, 1536, 4096, 9), (32, 1920, 4096, 12),
     (7, 8192, 4096, 15), (32, 14336, 4096, 15), (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15),
     (32, 8192, 1024, 16), (1, 12288, 2048, 16), (32, 12288, 2048, 16), (64, 12288, 2048, 16), (7, 16384, 1024, 16), (32, 8192, 3072, 16),   # a longer part costs more
+    (33, 768, 6144, 4), (32, 1024, 12288, 4), (48, 1024, 5120, 4), (16, 1024, 12288, 5), (40, 2048, 5120, 5),                 # four are summed in one go
     (7, 4096, 1024, 16), (7, 5120, 4096, 16), (7, 5120, 5120, 10)])                                                               # half megabytes do not show
 def test_dense_splits(L, M, K, N, S):
     """How many workgroups share K of a dense linear: uneven splits where even ones would start whole megabytes apart and the workgroups' parts are short or the
