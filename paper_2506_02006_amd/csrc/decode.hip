@@ -397,7 +397,7 @@ static DecodePlan plan_small(int q, int M, int K, int N, int native)
     const int halves = T / 8 > 0 ? T / 8 : 1;
     int S;
     if (q == 0) {
-        // Dense weights are shared out in k-steps: four per workgroup are enough (7 rows, us, with eight -> four: 2048 x 2048 7.32 -> 5.95,
+        // Dense weights can be shared out in k-steps (dense_by_steps): four per workgroup are enough (7 rows, us, with eight -> four: 2048 x 2048 7.32 -> 5.95,
         // 1024 x 4096 6.91 -> 6.01, 3072 x 3072 8.20 -> 7.84); where eight would leave one workgroup, one it stays (no workspace needed).
         S = split_for(halves > 1 ? T / 4 : 1);
         // Splits that all start a multiple of 1 MB apart read the same channels at the same time.  One fewer makes their parts uneven; at 128

@@ -456,7 +456,9 @@ static dim3 dequantize_grid(int K, int N)
 
 // Wide workgroups (32 units, 512 threads) read whole kilobytes of a row of fp32; below two of them per compute unit
 // the narrow ones (16 units) spread the matrix over twice as many.  Narrow / wide, us to 4 bits: bfloat16 1024 x 1288 4.7 / 5.4 (48 wide tiles),
-// 4096 x 4096 11.5 / 10.8 (512), 4096 x 22016 44.0 / 39.5; fp16 4.7 / 5.9, 11.6 / 11.9, 42.8 / 41.0; fp32 6.7 / 8.7, 16.2 / 16.2, 87.7 / 77.7.
+// 4096 x 22016 44.0 / 39.5 (2752); fp16 4.7 / 5.9, 42.8 / 41.0; fp32 6.7 / 8.7, 87.7 / 77.7.  The line is the one of wide matrices: of at most 4096 columns and 512 tiles
+// and more, fp16 would be 1 to 8 % faster on narrow ones (8192 x 2048 11.4 / 12.0, 11008 x 4096 22.8 / 23.4), bfloat16 from 6 % slower to 1 % faster (4096 x 4096
+// 11.5 / 10.8, 11008 x 4096 21.9 / 22.1) and fp32 up to 3 % faster (8192 x 2048 16.9 / 17.2).
 template <int BITS, int QU>
 static void quantize_units(const void* w, int dtype, uint32_t* qweight, half_t* sc, uint32_t* qzeros, void* native, int K, int N, hipStream_t st)
 {

@@ -16,8 +16,13 @@ def B():
     if not torch.cuda.is_available():
         pytest.skip("needs a GPU")
     from paper_2506_02006_amd import binding
-    yield binding
-    binding.set_tuning(binding.TUNE_DECODE_SPLIT, 0)
+    return binding
+
+
+@pytest.fixture(autouse=True)
+def planned_splits(B):
+    yield
+    B.set_tuning(B.TUNE_DECODE_SPLIT, 0)
 
 
 @pytest.mark.parametrize("fmt", ["fp16", "bf16"])
@@ -46,9 +51,8 @@ def test_dense_k_steps_left_over(B, oracle, K, splits, M, fmt):
 @pytest.mark.parametrize("fmt", ["fp16", "bf16"])
 @pytest.mark.parametrize("K,N", [(256, 264), (512, 264), (1024, 4096), (2048, 4096), (4096, 2048), (8192, 2048)])
 def test_dense_splits_as_planned(B, oracle, K, N, fmt):
-    """The planner's own splits where they changed their number: workgroups of four k-steps, and the splits whose starts lie whole megabytes apart."""
+    """Results on the planner's own splits (test_abi.py has their numbers): workgroups of four k-steps, and the splits whose starts lie whole megabytes apart."""
     dt = torch.float16 if fmt == "fp16" else torch.bfloat16
-    B.set_tuning(B.TUNE_DECODE_SPLIT, 0)
     g = torch.Generator().manual_seed(K + N)
     x, w = torch.randn((64, K), generator=g).to(dt), (0.05 * torch.randn((K, N), generator=g)).to(dt)
     want = (x.double() @ w.double()).numpy()
