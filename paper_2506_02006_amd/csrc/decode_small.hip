@@ -77,7 +77,7 @@ struct SmallTail {
 // memory before the first load could be issued.  Packed two to a dword:
 //   ms = M | S << 16;  qr = groups per split | (splits that take one more) << 16 (dense: k-steps or groups per split | (...) << 28);
 //   tiles_sl = column tiles of 256 | sl_shift << 16 (0: one slice of rows; 1: two slices of 32 rows, workgroups
-//   (tile, slice, split));  inv_s = ceil(65536 / S): j / S = (j * inv_s) >> 16 for the j that occur.
+//   (tile, slice, split)) | runs << 17 (place_of);  inv_s = ceil(65536 / S): j / S = (j * inv_s) >> 16 for the j that occur.
 
 template <bool BF>
 __device__ __forceinline__ f32x4 mfma_small(half8_t a, half8_t b, f32x4 c)
@@ -106,20 +106,25 @@ __device__ __forceinline__ void reload_fence() { asm volatile("" ::: "memory"); 
 // Which (column tile, slice of rows, split) a workgroup is.  Workgroup L runs on XCD L % 8 (workgroups
 // are dealt to the XCDs in turn).  The S workgroups of a unit = (tile, slice) are given the same L % 8,
 // so that they meet in one L2, and so are the two slices of a tile, which read the same weights:
-// within XCD `xcd` the workgroups j = L / 8 walk (tile slot, slice, split), tile = 8 * slot + xcd.
+// within XCD `xcd` the workgroups j = L / 8 walk (tile slot, slice, split), tile = 8 * slot + xcd -- or, with `runs`, tile
+// slot of the XCD's own run of neighbouring tiles (neighbour_runs says when; the XCDs carry the same number of tiles either way).
 // Tiles that do not exist (the last slot of an XCD when the tile count is no multiple of 8) have
 // tile >= tiles and leave at once.
 struct Place { int tile, slice, sp, unit; };
 __device__ __forceinline__ Place place_of(int tiles_sl, int inv_s, int S)
 {
     const int L = blockIdx.x, xcd = L & 7, jj = L >> 3;
-    const int sl_shift = tiles_sl >> 16;
+    const int sl_shift = (tiles_sl >> 16) & 1;
     const int pair = (jj * inv_s) >> 16;
     Place p;
     p.sp = jj - pair * S;
     const int slot = pair >> sl_shift;
     p.slice = pair - (slot << sl_shift);
     p.tile = slot * 8 + xcd;
+    if (tiles_sl >> 17) {
+        const int tiles = tiles_sl & 0xFFFF, each = tiles >> 3, more = tiles & 7;   // the first `more` XCDs have one tile more
+        p.tile = slot < each + (xcd < more ? 1 : 0) ? xcd * each + (xcd < more ? xcd : more) + slot : tiles;
+    }
     p.unit = (p.tile << sl_shift) + p.slice;
     return p;
 }
@@ -1416,6 +1421,18 @@ bool dense_by_steps(int M, int K, int S, int tiles)
     return M > 32 ? (most + 1) / 2 < 16 : T != 4 * S || tiles * S <= 160;
 }
 
+// Whether neighbouring tiles go to one XCD instead of being dealt out to all: where the rows of the stored matrix do not start on cache lines, the piece
+// of a row that a tile reads shares its first and last line with the neighbours' pieces, and two XCDs each fetch that line from memory for themselves (a fifth
+// to a half more bytes, the narrower the piece).  Dealt out -> in runs, us: dense 4224 x 11016 at 7 rows 23.8 -> 21.6, at 32 rows 27.4 -> 25.9; 4-bit
+// 4224 x 11016 at 1 row 11.4 -> 9.9, at 16 rows 13.4 -> 12.25; 8-bit 4224 x 11016 at 1 row 19.7 -> 17.4, 4096 x 28680 38.0 -> 30.9, at 16 rows 40.2 -> 34.9.
+// On lines there is nothing to share, and dense weights ran up to 3 % slower in runs (11008 x 4096 at 1 row 18.0 -> 18.6, 5120 x 5120 13.8 -> 14.0); with
+// fewer than twelve tiles most have no neighbour on their XCD (4-bit 1664 x 2056, nine tiles, at 16 rows 6.97 -> 7.2); the native code order has no rows.
+bool neighbour_runs(const SmallArgs& a)
+{
+    const long long row_bits = (long long)a.N * (a.dense ? 16 : a.w8 ? 8 : 4);
+    return !a.native && a.tiles >= 12 && row_bits % (8 * 128) != 0;
+}
+
 template <class Kernel>
 hipError_t launch_small_with(Kernel kernel, int waves, const SmallArgs& a, hipStream_t st, bool by_steps = false)
 {
@@ -1427,7 +1444,7 @@ hipError_t launch_small_with(Kernel kernel, int waves, const SmallArgs& a, hipSt
     const int grid = 8 * ((a.tiles + 7) / 8) * a.S << sl_shift;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * 64), 0, st,
                        (const uint32_t*)a.w, a.x, a.scales, (const uint32_t*)a.qzeros, a.K, a.N, a.M | (a.S << 16), q | (int)((uint32_t)r << (a.dense ? 28 : 16)),
-                       a.tiles | (sl_shift << 16), (65536 + a.S - 1) / a.S, t);
+                       a.tiles | (sl_shift << 16) | (neighbour_runs(a) ? 1 << 17 : 0), (65536 + a.S - 1) / a.S, t);
     return hipGetLastError();
 }
 
