@@ -63,6 +63,7 @@ constexpr int kAhead   = 3;                      // k-steps a load runs ahead of
 // sums are in place) + where those sums can be read: 0 = in memory, 1 + x = in the L2 of XCD x.  A
 // reader compares the counter with the value it found when it started.
 constexpr int kCtlInts = kSmallCtlInts;
+constexpr uint32_t kNoColumn = 0xFFFFFF00u;      // a column beyond N: stores there are dropped
 
 struct SmallTail {
     void*     y;
@@ -132,7 +133,7 @@ __device__ __forceinline__ Place place_of(int tiles_sl, int inv_s, int S)
 // ---- what follows the k loop: the hand-over between the S workgroups of a unit ----
 // run_pass(sink) runs the k loop of the split begin_pass() was last called for (the caller has called
 // it for this workgroup's own split) and hands every vector (four rows of one column) of the unit's
-// nvec, summed over the waves, to sink(id, value); store_y(id, value) writes a finished vector.
+// nvec, summed over the waves, to sink(id, value); place_y(id) is where its first row is in y (ry), in bytes.
 //   Every workgroup puts its partial vectors into its slot, waits for the stores to be acknowledged
 // and raises its flag's counter by one.  Then it polls the S flags of the unit (one load per look),
 // and when every counter differs from what it was when this workgroup started (`base`, read by the
@@ -152,12 +153,17 @@ __device__ __forceinline__ Place place_of(int tiles_sl, int inv_s, int S)
 // whose flag did not move, and puts that split's vectors of its share where the split's owner puts
 // them (the same numbers from the same instructions: if both write, they write the same bits).
 // Whoever adds a vector up, and wherever the terms come from, they are added in split order.
-template <class RunPass, class BeginPass, class StoreY>
+template <bool BF, class RunPass, class BeginPass, class PlaceY>
 __device__ __forceinline__ void finish_over_splits(const SmallTail& t, int S, const Place& p, int nvec, uint32_t base,
-                                                   uint32_t* fresh_word, RunPass&& run_pass, BeginPass&& begin_pass, StoreY&& store_y)
+                                                   uint32_t* fresh_word, const __amdgpu_buffer_rsrc_t ry, uint32_t row_bytes, RunPass&& run_pass, BeginPass&& begin_pass, PlaceY&& place_y)
 {
+    // four rows of a column; rows that do not exist lie past the buffer (32 rows at most, of fewer than 2^26 columns: the offsets do not wrap)
+    auto store_y = [&](uint32_t off, f32x4 acc) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) __builtin_amdgcn_raw_buffer_store_b16(narrow16<BF>(acc[r]), ry, off == kNoColumn ? off : off + r * row_bytes, 0, 0);
+    };
     if (S == 1) {
-        run_pass([&](int id, f32x4 v) { store_y(id, v); });
+        run_pass([&](int id, f32x4 v) { store_y(place_y(id), v); });
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63;
@@ -179,6 +185,15 @@ __device__ __forceinline__ void finish_over_splits(const SmallTail& t, int S, co
     };
     run_pass([&](int id, f32x4 v) { put(sp, id, v); });
     MORPH_TICK(3);                                       // all waves done, partial sums on their way
+    // where this thread's first vector of the share is read and stored: made while the stores are under way (a lone wave gets an instruction that needs the
+    // one before done every 3.5 ns, and nothing overlaps with what follows the wait)
+    uint32_t from[16], first_y = place_y(v0 + tid);      // byte offset of split q (beyond S: of the last one, not added)
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        from[q] = (uint32_t)(q < S ? q : S - 1) * slot_bytes;
+        asm volatile("" : "+s"(from[q]));
+    }
+    asm volatile("" : "+v"(first_y));
     wait_stores();
     __syncthreads();
     MORPH_TICK(4);                                       // partials in place
@@ -217,24 +232,26 @@ __device__ __forceinline__ void finish_over_splits(const SmallTail& t, int S, co
     }
 
     // ---- my share: every vector summed over the splits in split order ----
+    // (offsets and y's buffer made before the wait, y through 32-bit offsets: 4-bit native 4096 x 4096, one row, from the last flag to the store 0.82 -> 0.57 us,
+    // the launch 5.5 -> 5.35; canonical 6.2 -> 6.0; 8-bit 8.5 -> 8.35)
     auto gather = [&](auto width) {
-        constexpr int W = decltype(width)::value;        // S <= W; splits beyond S lie past the buffer and read as zeros
-        for (int id = v0 + tid; id < v1; id += (int)blockDim.x) {
+        constexpr int W = decltype(width)::value;        // S <= W
+        auto sum = [&](int id) {
             u32x4 v[W];
             reload_fence();
 #pragma unroll
-            for (int q = 0; q < W; q++) {
-                const uint32_t off = q < S ? (uint32_t)q * slot_bytes + (uint32_t)id * 16u : 0xFFFFFFF0u;
-                v[q] = __builtin_amdgcn_raw_buffer_load_b128(rp, off, 0, kAuxSystemScope);
-            }
+            for (int q = 0; q < W; q++) v[q] = __builtin_amdgcn_raw_buffer_load_b128(rp, (uint32_t)id * 16u, from[q], kAuxSystemScope);
             f32x4 acc = zero4;
 #pragma unroll
             for (int q = 0; q < W; q++)
                 if (q < S) acc += bit_cast<f32x4>(v[q]);
-            store_y(id, acc);
-        }
+            return acc;
+        };
+        if (v0 + tid < v1) store_y(first_y, sum(v0 + tid));
+        for (int id = v0 + tid + (int)blockDim.x; id < v1; id += (int)blockDim.x) store_y(place_y(id), sum(id));
     };
     if (S <= 4) gather(std::integral_constant<int, 4>{});
+    else if (S <= 8) gather(std::integral_constant<int, 8>{});
     else gather(std::integral_constant<int, 16>{});
     MORPH_TICK(6);                                       // own share stored
 }
@@ -371,16 +388,8 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_small_kernel(
         for (int q = 1; q < kSmWaves; q++) a += yl[(q * 64 + ln) * 16 + j];
         return a;
     };
-    uint16_t* y = (uint16_t*)t.y;
-    auto vec_store_y = [&](int id, f32x4 acc) {
-        const int ln = id >> 4, j = id & 15;
-        const int col = n0 + 16 * (ln & 15) + j, row = 4 * (ln >> 4);
-        if (col < N) {
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                if (row + r < M) y[(size_t)(row + r) * N + col] = narrow16<BF>(acc[r]);
-        }
-    };
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(t.y, (uint32_t)M * (uint32_t)N * 2u);
+    auto place_y = [&](int id) { return n0 + (id & 255) < N ? (uint32_t)(4 * (id >> 8) * N + n0 + (id & 255)) * 2u : kNoColumn; };
 
     auto run_pass = [&](auto&& sink) {
         // Two sets of group sums: while the MFMAs of a group fill one set, the sums of the group before are
@@ -510,7 +519,7 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_small_kernel(
         for (int id = tid; id < nvec; id += kSmWaves * 64) sink(id, vec_sum(id));
     };
 
-    finish_over_splits(t, S, p, nvec, base, &fresh_word, run_pass, begin_pass, vec_store_y);
+    finish_over_splits<BF>(t, S, p, nvec, base, &fresh_word, ry, (uint32_t)N * 2u, run_pass, begin_pass, place_y);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -618,16 +627,8 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_small8_kernel(
         for (int q = 1; q < kSmWaves; q++) a += yl[(q * 64 + ln) * 8 + j];
         return a;
     };
-    uint16_t* y = (uint16_t*)t.y;
-    auto vec_store_y = [&](int id, f32x4 acc) {
-        const int ln = id >> 3, j = id & 7;
-        const int col = n0 + 8 * (ln & 15) + j, row = 4 * (ln >> 4);
-        if (col < N) {
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                if (row + r < M) y[(size_t)(row + r) * N + col] = narrow16<BF>(acc[r]);
-        }
-    };
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc(t.y, (uint32_t)M * (uint32_t)N * 2u);
+    auto place_y = [&](int id) { return n0 + (id & 127) < N ? (uint32_t)(4 * (id >> 7) * N + n0 + (id & 127)) * 2u : kNoColumn; };
 
     auto run_pass = [&](auto&& sink) {
         f32x4 gacc[8], xs = zero4;                       // sums over the open group: x * code of column j; row sums of x
@@ -699,7 +700,7 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_small8_kernel(
         for (int id = tid; id < nvec; id += kSmWaves * 64) sink(id, vec_sum(id));
     };
 
-    finish_over_splits(t, S, p, nvec, base, &fresh_word, run_pass, begin_pass, vec_store_y);
+    finish_over_splits<BF>(t, S, p, nvec, base, &fresh_word, ry, (uint32_t)N * 2u, run_pass, begin_pass, place_y);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -836,15 +837,8 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_mid_kernel(
     // A vector = four rows of one column; vector (mt, rq, col): column n0 + col, rows 16 mt + 4 rq ..;
     // its number is id = 1024 mt + 256 rq + col.
     constexpr int nvec = 2048;
-    uint16_t* y = (uint16_t*)t.y + (size_t)(32 * p.slice) * N;
-    auto vec_store_y = [&](int id, f32x4 acc) {
-        const int col = n0 + (id & 255), row = 4 * (id >> 8);
-        if (col < N) {
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                if (row + r < M) y[(size_t)(row + r) * N + col] = narrow16<BF>(acc[r]);
-        }
-    };
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc((uint16_t*)t.y + (size_t)(32 * p.slice) * N, (uint32_t)M * (uint32_t)N * 2u);
+    auto place_y = [&](int id) { return n0 + (id & 255) < N ? (uint32_t)(4 * (id >> 8) * N + n0 + (id & 255)) * 2u : kNoColumn; };
 
     auto run_pass = [&](auto&& sink) {
         // Two sets of group sums: while the MFMAs of a group fill one set, the sums of the group before are
@@ -984,7 +978,7 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_mid_kernel(
         }
     };
 
-    finish_over_splits(t, S, p, nvec, base, &fresh_word, run_pass, begin_pass, vec_store_y);
+    finish_over_splits<BF>(t, S, p, nvec, base, &fresh_word, ry, (uint32_t)N * 2u, run_pass, begin_pass, place_y);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1123,15 +1117,8 @@ __global__ __launch_bounds__(kWideWaves * 64) void decode_wide_kernel(
     // A vector = four rows of one column; vector (mt, rq, col): column n0 + col, rows 16 mt + 4 rq ..;
     // its number is id = 1024 mt + 256 rq + col.  With one tile of rows only the groups of four rows that exist are numbered.
     const int nvec = RT == 1 ? 256 * t.nb : 1024 * RT;
-    uint16_t* y = (uint16_t*)t.y + (size_t)(32 * p.slice) * N;
-    auto vec_store_y = [&](int id, f32x4 acc) {
-        const int col = n0 + (id & 255), row = 4 * (id >> 8);
-        if (col < N) {
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                if (row + r < M) y[(size_t)(row + r) * N + col] = narrow16<BF>(acc[r]);
-        }
-    };
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc((uint16_t*)t.y + (size_t)(32 * p.slice) * N, (uint32_t)M * (uint32_t)N * 2u);
+    auto place_y = [&](int id) { return n0 + (id & 255) < N ? (uint32_t)(4 * (id >> 8) * N + n0 + (id & 255)) * 2u : kNoColumn; };
 
     auto run_pass = [&](auto&& sink) {
         // gacc[mt][2 yb]: sum of x * byte, gacc[mt][2 yb + 1]: sum of x * (byte & 0xF0) over the open group,
@@ -1235,7 +1222,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void decode_wide_kernel(
         }
     };
 
-    finish_over_splits(t, S, p, nvec, base, &fresh_word, run_pass, begin_pass, vec_store_y);
+    finish_over_splits<BF>(t, S, p, nvec, base, &fresh_word, ry, (uint32_t)N * 2u, run_pass, begin_pass, place_y);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1337,15 +1324,8 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     // A vector = four rows of one column; vector (mt, rq, col): column n0 + col, rows 16 mt + 4 rq ..;
     // its number is id = 1024 mt + 256 rq + col.  With one tile of rows only the groups of four rows that exist are numbered.
     const int nvec = MT == 2 ? 2048 : 256 * t.nb;
-    uint16_t* y = (uint16_t*)t.y + (size_t)(32 * p.slice) * N;
-    auto vec_store_y = [&](int id, f32x4 acc) {
-        const int col = n0 + (id & 255), row = 4 * (id >> 8);
-        if (col < N) {
-#pragma unroll
-            for (int r = 0; r < 4; r++)
-                if (row + r < M) y[(size_t)(row + r) * N + col] = narrow16<BF>(acc[r]);
-        }
-    };
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc((uint16_t*)t.y + (size_t)(32 * p.slice) * N, (uint32_t)M * (uint32_t)N * 2u);
+    auto place_y = [&](int id) { return n0 + (id & 255) < N ? (uint32_t)(4 * (id >> 8) * N + n0 + (id & 255)) * 2u : kNoColumn; };
 
     auto run_pass = [&](auto&& sink) {
         f32x4 acc[MT][8];                                // column j of the lane, rows 16 mt + 4 b ..
@@ -1403,7 +1383,7 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
         }
     };
 
-    finish_over_splits(t, S, p, nvec, base, &fresh_word, run_pass, begin_pass, vec_store_y);
+    finish_over_splits<BF>(t, S, p, nvec, base, &fresh_word, ry, (uint32_t)N * 2u, run_pass, begin_pass, place_y);
 }
 
 // Whether dense weights are shared out in k-steps instead of runs of 128 rows, of which the slowest half of a workgroup's waves has up to three steps more
