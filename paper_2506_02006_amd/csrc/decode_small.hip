@@ -157,7 +157,7 @@ template <bool BF, class RunPass, class BeginPass, class PlaceY>
 __device__ __forceinline__ void finish_over_splits(const SmallTail& t, int S, const Place& p, int nvec, uint32_t base,
                                                    uint32_t* fresh_word, const __amdgpu_buffer_rsrc_t ry, uint32_t row_bytes, RunPass&& run_pass, BeginPass&& begin_pass, PlaceY&& place_y)
 {
-    // four rows of a column; rows that do not exist lie past the buffer (32 rows at most, of fewer than 2^26 columns: the offsets do not wrap)
+    // four rows of a column; rows that do not exist lie past the buffer (32 rows at most, of fewer than 2^26 columns, or 64 of fewer than 2^23: the offsets do not wrap)
     auto store_y = [&](uint32_t off, f32x4 acc) {
 #pragma unroll
         for (int r = 0; r < 4; r++) __builtin_amdgcn_raw_buffer_store_b16(narrow16<BF>(acc[r]), ry, off == kNoColumn ? off : off + r * row_bytes, 0, 0);
@@ -1227,11 +1227,16 @@ __global__ __launch_bounds__(kWideWaves * 64) void decode_wide_kernel(
 
 // ------------------------------------------------------------------------------------------------
 // Dense weights (fp16, or bfloat16 with BF), M <= 64: the skeleton of decode_mid_kernel -- wave (kh, ch),
-// x through LDS, two slices of 32 rows beyond 32, the same vectors and the same hand-over -- around a
+// x through LDS, two slices of 32 rows beyond 32 (but see MT = 4), the same vectors and the same hand-over -- around a
 // loop with nothing to unpack and nothing to fold.  A lane loads its 8 columns (16 bytes) of 8
 // consecutive rows, pairs the 16-bit values of rows 2 q, 2 q + 1 column by column (v_perm_b32: the MFMA
 // wants 8 consecutive k of one column), and the accumulators are the running results.  MT: tiles of 16
 // rows per slice (1: M <= 16).  A k-step is 8 KB per wave, three of them in flight.
+// MT = 4: all of 33 .. 64 rows in one slice, so that the matrix is read once (plan_one_pass says where).  The four waves then take a quarter of K each over 128
+// columns: the accumulators fill as many registers as those of 32 rows x 256 columns would twice over, and no two waves load the same x.  x comes in groups of 64 k, half of the
+// next one requested in each of its two steps: whole groups of 128 k, or both halves at once, do not fit the registers beside three k-steps of weights, and what
+// was spilled of them at the start held the first weights back (4096 x 4096 17.0 us instead of 14.1, 5120 x 5120 19.6 instead of 18.7); groups of 32 k, half a
+// cache line of each row, read x twice (5120 x 27648 at 64 rows 69.5 us instead of 61.3).
 // Bound: memory, in pieces of 512 bytes of a row (a read of the same pieces by as many workgroups and nothing else: 4096 x 12288 17.4 us,
 // 4096 x 22016 33.0, 11008 x 4096 15.9), the start and the hand-over.
 // STEPS: K is shared out in k-steps instead of the runs of 128 rows that the quantized kernels walk; up to three steps are left after the last round of four
@@ -1247,22 +1252,27 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     int tiles_sl, int inv_s, SmallTail t)
 {
     const int M_all = ms & 0xFFFF, S = ms >> 16, q_units = qr & 0x0FFFFFFF, r_units = (int)((uint32_t)qr >> 28);
-    // as in decode_mid_kernel: per wave two buffers of x (16 MT rows of 128 k, pieces XOR-swizzled by the row),
+    // as in decode_mid_kernel: per wave two buffers of x (16 MT rows of 128 k, MT = 4: of 64 k; pieces XOR-swizzled by the row),
     // afterwards the results of one tile of 16 rows at a time
-    __shared__ __align__(16) u32x4 sm[kSmWaves * 1024];
+    constexpr int XU = MT == 4 ? 2 : kRing;              // k-steps of an x group
+    constexpr int PC = 4 * XU, XB = 512;                 // pieces of 16 bytes of a row of it, and of a buffer
+    constexpr int RL = 64 / PC, XL = 16 * MT / RL;       // rows of a load, and loads
+    constexpr int XH = MT == 4 ? 2 : 1;                  // parts a group is requested in
+    __shared__ __align__(16) u32x4 sm[kSmWaves * 2 * XB];
     __shared__ uint32_t fresh_word;
 
     MORPH_TICK(0);                                       // kernel entry
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kh = wave >> 1, ch = wave & 1;
+    constexpr int CW = MT == 4 ? 1 : 2, KH = kSmWaves / CW;   // waves side by side, and shares of K
+    constexpr int TW = 128 * CW;                         // columns of a tile
+    const int kh = wave / CW, ch = wave % CW;
     const int c = lane & 15, b = lane >> 4;
     const int tiles = tiles_sl & 0xFFFF;
     const Place p = place_of(tiles_sl, inv_s, S);
     if (p.tile >= tiles) return;
-    const int n0 = p.tile * 256;
-    constexpr int ROWS = 16 * MT;                        // rows of a slice
-    const int M = M_all - 32 * p.slice < ROWS ? M_all - 32 * p.slice : ROWS;
+    const int n0 = p.tile * TW;
+    const int M = MT == 4 || M_all - 32 * p.slice < 16 * MT ? M_all - 32 * p.slice : 16 * MT;     // MT = 4: one slice
     const uint16_t* x = (const uint16_t*)x_all + (size_t)(32 * p.slice) * K;
 
     const uint32_t row_bytes = (uint32_t)N * 2u;
@@ -1272,13 +1282,13 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     const uint32_t kOut = 0xFFFFFFF0u;
     const uint32_t voff_w = ncol < N ? (uint32_t)(8 * b) * row_bytes + (uint32_t)ncol * 2u : kOut;
     // x of a whole group: load i takes rows 4 i + (lane >> 4), piece (lane & 15) of each; rows at or beyond M lie past the buffer
-    const uint32_t voff_x = ((uint32_t)b * (uint32_t)K + 8u * (uint32_t)c) * 2u;
+    const uint32_t voff_x = ((uint32_t)(lane / PC) * (uint32_t)K + 8u * (uint32_t)(lane % PC)) * 2u;
     const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-    u32x4* const xl = sm + wave * 1024;
+    u32x4* const xl = sm + wave * 2 * XB;
 
     int        ks0 = 0, ks1 = 0;                         // this wave's k-steps
     DenseStage st[kRing];
-    u32x4      xg[4 * MT];
+    u32x4      xg[XL];
     auto load_stage = [&](DenseStage& sg, int ks) {
         const bool     dead = ks >= ks1;
         const uint32_t so   = dead ? 0u : (uint32_t)ks * 32u * row_bytes;
@@ -1286,18 +1296,19 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
 #pragma unroll
         for (int i = 0; i < 8; i++) sg.r[i] = buf_load_u32x4<kAuxStream>(rw, vw, so + (uint32_t)i * row_bytes);
     };
-    auto load_xgroup = [&](int ks) {                     // 128 k from step ks on (beyond the end of K: the next row's, never used)
+    auto swz = [](int row) { return MT == 4 ? (row >> 1) & 7 : row & 15; };
+    auto load_xgroup = [&](int ks, int h0, int h1) {     // parts h0 .. h1 - 1 of the group from step ks on (beyond the end of K: the next row's, never used)
         const bool     dead = ks >= ks1;
         const uint32_t dm   = dead ? kOut : 0u;
 #pragma unroll
-        for (int i = 0; i < 4 * MT; i++)
-            xg[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (voff_x + (uint32_t)i * 8u * (uint32_t)K) | dm, dead ? 0u : (uint32_t)ks * 64u, 0);
+        for (int i = h0 * XL / XH; i < h1 * XL / XH; i++)
+            xg[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (voff_x + (uint32_t)i * (uint32_t)(2 * RL) * (uint32_t)K) | dm, dead ? 0u : (uint32_t)ks * 64u, 0);
     };
-    auto store_xgroup = [&](int buf) {
+    auto store_xgroup = [&](int buf, int h0, int h1) {
 #pragma unroll
-        for (int i = 0; i < 4 * MT; i++) {
-            const int row = 4 * i + b;
-            xl[buf * 512 + row * 16 + ((c ^ row) & 15)] = xg[i];
+        for (int i = h0 * XL / XH; i < h1 * XL / XH; i++) {
+            const int row = RL * i + lane / PC;
+            xl[buf * XB + row * PC + ((lane ^ swz(row)) & (PC - 1))] = xg[i];
         }
     };
     auto begin_pass = [&](int split) {
@@ -1305,9 +1316,9 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
         constexpr int U = STEPS ? 1 : kRing;
         const int kb = split * q_units + (split < r_units ? split : r_units);
         const int nk = q_units + (split < r_units ? 1 : 0);
-        ks0 = U * (kb + ((kh * nk) >> 1));
-        ks1 = U * (kb + (((kh + 1) * nk) >> 1));
-        load_xgroup(ks0);
+        ks0 = U * (kb + (kh * nk) / KH);
+        ks1 = U * (kb + ((kh + 1) * nk) / KH);
+        load_xgroup(ks0, 0, XH);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 0; i < kAhead; i++) {
@@ -1322,10 +1333,10 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     MORPH_TICK(1);                                       // first loads issued
 
     // A vector = four rows of one column; vector (mt, rq, col): column n0 + col, rows 16 mt + 4 rq ..;
-    // its number is id = 1024 mt + 256 rq + col.  With one tile of rows only the groups of four rows that exist are numbered.
-    const int nvec = MT == 2 ? 2048 : 256 * t.nb;
+    // its number is id = (4 mt + rq) TW + col.  With one tile of rows only the groups of four rows that exist are numbered.
+    const int nvec = MT == 1 ? TW * t.nb : 4 * TW * MT;
     const __amdgpu_buffer_rsrc_t ry = make_rsrc((uint16_t*)t.y + (size_t)(32 * p.slice) * N, (uint32_t)M * (uint32_t)N * 2u);
-    auto place_y = [&](int id) { return n0 + (id & 255) < N ? (uint32_t)(4 * (id >> 8) * N + n0 + (id & 255)) * 2u : kNoColumn; };
+    auto place_y = [&](int id) { return n0 + id % TW < N ? (uint32_t)(4 * (id / TW) * N + n0 + id % TW) * 2u : kNoColumn; };
 
     auto run_pass = [&](auto&& sink) {
         f32x4 acc[MT][8];                                // column j of the lane, rows 16 mt + 4 b ..
@@ -1338,7 +1349,7 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
         auto multiply = [&](const DenseStage& sg, int u) {
             half8_t xa[MT];
 #pragma unroll
-            for (int mt = 0; mt < MT; mt++) xa[mt] = bit_cast<half8_t>(xl[xb * 512 + (16 * mt + c) * 16 + ((4 * u + b) ^ c)]);
+            for (int mt = 0; mt < MT; mt++) xa[mt] = bit_cast<half8_t>(xl[xb * XB + (16 * mt + c) * PC + ((4 * (u % XU) + b) ^ swz(c))]);
 #pragma unroll
             for (int j = 0; j < 8; j++) {
                 u32x4 bo;
@@ -1349,36 +1360,44 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
                 for (int mt = 0; mt < MT; mt++) acc[mt][j] = mfma_small<BF>(xa[mt], bit_cast<half8_t>(bo), acc[mt][j]);
             }
         };
-        store_xgroup(0);
+        store_xgroup(0, 0, XH);
         int ks = ks0;                                    // rounds of four steps = 128 k of x
         for (; STEPS ? ks + kRing <= ks1 : ks < ks1; ks += kRing) {
 #pragma unroll
             for (int u = 0; u < kRing; u++) {
                 load_stage(st[(u + kAhead) % kRing], ks + u + kAhead);
-                if (u == 0) load_xgroup(ks + kRing);
+                if (u % XU < XH) load_xgroup(ks + u - u % XU + XU, u % XU, u % XU + 1);
                 __builtin_amdgcn_sched_barrier(0);
                 multiply(st[u], u);
                 __builtin_amdgcn_sched_barrier(0);
+                if (XH > 1 || u == XU - 1) store_xgroup(xb ^ 1, u % XH, u % XH + 1);
+                if (u % XU == XU - 1) xb ^= 1;           // the next group's x, requested during this one
             }
-            store_xgroup(xb ^ 1);                        // the next round's x, requested at the top of this one
-            xb ^= 1;
         }
         if constexpr (STEPS) {                           // up to three more: they were requested by the last round (or by begin_pass)
-            if (ks < ks1) multiply(st[0], 0);
-            if (ks + 1 < ks1) multiply(st[1], 1);
-            if (ks + 2 < ks1) multiply(st[2], 2);
+#pragma unroll
+            for (int u = 0; u < kAhead; u++) {
+                if (ks + u >= ks1) break;
+                if (XU == 2 && u < 2) load_xgroup(ks + 2, u, u + 1);
+                multiply(st[u], u);
+                if (XU == 2 && u < 2) store_xgroup(xb ^ 1, u, u + 1);
+                if (XU == 2 && u == 1) xb ^= 1;
+            }
         }
-        // one tile of 16 rows at a time through LDS, summed over the two halves of K
+        // one tile of 16 rows at a time through LDS, summed over the waves' shares of K
 #pragma unroll
         for (int mt = 0; mt < MT; mt++) {
             __syncthreads();                             // every wave is done with its x, or with the tile before
 #pragma unroll
-            for (int j = 0; j < 8; j++) sm[kh * 1024 + b * 256 + ch * 128 + c * 8 + (j ^ (c & 7))] = bit_cast<u32x4>(acc[mt][j]);
+            for (int j = 0; j < 8; j++) sm[kh * 4 * TW + b * TW + ch * 128 + c * 8 + (j ^ (c & 7))] = bit_cast<u32x4>(acc[mt][j]);
             __syncthreads();
-            const int live = MT == 2 ? 1024 : 256 * t.nb;
+            const int live = MT == 1 ? TW * t.nb : 4 * TW;
             for (int lid = tid; lid < live; lid += kSmWaves * 64) {
                 const int pos = (lid & ~7) | ((lid ^ (lid >> 3)) & 7);      // column 8 c + j sits at j ^ (c & 7)
-                sink(mt * 1024 + lid, bit_cast<f32x4>(sm[pos]) + bit_cast<f32x4>(sm[1024 + pos]));
+                f32x4 v = bit_cast<f32x4>(sm[pos]);
+#pragma unroll
+                for (int h = 1; h < KH; h++) v += bit_cast<f32x4>(sm[h * 4 * TW + pos]);
+                sink(4 * TW * mt + lid, v);
             }
         }
     };
@@ -1420,7 +1439,7 @@ hipError_t launch_small_with(Kernel kernel, int waves, const SmallArgs& a, hipSt
     SmallTail t;
     t.y = a.y; t.slots = a.slots; t.ctl = a.ctl; t.polls = a.polls; t.nb = (a.M + 3) / 4;
     t.far = a.far;
-    const int sl_shift = a.M > 32 ? 1 : 0;
+    const int sl_shift = a.slices > 1 ? 1 : 0;
     const int grid = 8 * ((a.tiles + 7) / 8) * a.S << sl_shift;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(waves * 64), 0, st,
                        (const uint32_t*)a.w, a.x, a.scales, (const uint32_t*)a.qzeros, a.K, a.N, a.M | (a.S << 16), q | (int)((uint32_t)r << (a.dense ? 28 : 16)),
@@ -1436,6 +1455,7 @@ hipError_t launch_small_m(const SmallArgs& a, hipStream_t st)
         return launch_small_with(decode_small8_kernel<4, BF>, kSmWaves, a, st);
     }
     if (a.dense) {
+        if (a.M > 32 && a.slices == 1) return launch_small_with(decode_dense_kernel<4, BF, true>, kSmWaves, a, st, true);
         if (dense_by_steps(a.M, a.K, a.S, a.tiles))
             return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, true>, kSmWaves, a, st, true) : launch_small_with(decode_dense_kernel<2, BF, true>, kSmWaves, a, st, true);
         return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, false>, kSmWaves, a, st) : launch_small_with(decode_dense_kernel<2, BF, false>, kSmWaves, a, st);
@@ -1462,7 +1482,8 @@ hipError_t launch_decode_small(const SmallArgs& a, hipStream_t st)
 {
     if (a.M < 1 || a.M > 64 || a.S < 1 || a.S > 16 || a.S > a.K / kGroup || a.tiles < 1 || a.tiles > 65535 || a.K / kGroup > 65535) return hipErrorInvalidValue;
     if (a.wide && !a.native) return hipErrorInvalidValue;
-    if (a.S > 1 && a.tiles * (a.M > 32 ? 2 : 1) > 256) return hipErrorInvalidValue;     // flags for 256 (tile, slice) pairs
+    if (a.slices != (a.M > 32 ? 2 : 1) && !(a.dense && a.M > 32 && a.slices == 1)) return hipErrorInvalidValue;
+    if (a.S > 1 && a.tiles * a.slices > 256) return hipErrorInvalidValue;     // flags for 256 (tile, slice) pairs
     if (a.dense && a.native) return hipErrorInvalidValue;
     if (a.w8 && (a.dense || a.native || a.wide || a.M > 16)) return hipErrorInvalidValue;
     return a.bf ? launch_small_m<true>(a, st) : launch_small_m<false>(a, st);
