@@ -363,14 +363,14 @@ DecodePlan plan_rows(int q, int M, int K, int N, int rows)
 // At most 16 rows of 4-bit weights: the kernel of decode_small.hip.  One workgroup per compute unit;
 // K is shared out over S <= 16 workgroups per column tile of 256 (one "share done" bit each in the
 // tile's counter), every workgroup keeping at least four k-steps, one per wave.
-// whole: dense weights with all of 33 .. 64 rows in one workgroup and column tiles of 128 (plan_one_pass).
-static DecodePlan plan_small(int q, int M, int K, int N, int native, bool whole = false)
+// narrow: dense weights in column tiles of 128, beyond 32 rows all rows in one workgroup (plan_narrow).
+static DecodePlan plan_small(int q, int M, int K, int N, int native, bool narrow = false)
 {
     DecodePlan pl{};
     pl.small  = 1;
     pl.rows   = 16;
     pl.slices = 1;
-    pl.tile_n = q == 2 || whole ? 128 : 256;             // 8-bit codes: a wave's 8 bytes per row are 8 columns
+    pl.tile_n = q == 2 || narrow ? 128 : 256;             // 8-bit codes: a wave's 8 bytes per row are 8 columns
     pl.tiles  = (N + pl.tile_n - 1) / pl.tile_n;
     const int T = K / 32;
     // Never more workgroups than compute units: the workgroups of a tile wait for each other's partial
@@ -378,7 +378,7 @@ static DecodePlan plan_small(int q, int M, int K, int N, int native, bool whole 
     // uses more than half the registers and the LDS of one).
     int target = tuning_get(TUNE_DECODE_WGS);
     if (target <= 0) target = prefill_compute_units();
-    const int slices = M > 32 && !whole ? 2 : 1;         // beyond 32 rows slices of 32 rows, a workgroup each
+    const int slices = M > 32 && !narrow ? 2 : 1;         // beyond 32 rows slices of 32 rows, a workgroup each
     // `most`: every workgroup keeps a quantization group (decode_small_kernel), or each half of its waves one
     auto split_for = [&](int most) {
         int S = target / (pl.tiles * slices);
@@ -418,7 +418,7 @@ static DecodePlan plan_small(int q, int M, int K, int N, int native, bool whole 
         }
         // The sum over up to four splits is read four wide, over more sixteen wide (finish_over_splits), which shows beyond 16 rows: four instead of five where the
         // slowest half of the waves has no more to walk then (us, 5 -> 4: 768 x 6144 at 33 rows 9.2 -> 8.6, 1024 x 12288 at 32 11.8 -> 10.95; at 1 row 8.17, 8.15).
-        const int shares = whole ? 4 : 2;                // of a part among the waves
+        const int shares = narrow ? 4 : 2;                // of a part among the waves
         auto slowest = [&](int s) { return ((T + s - 1) / s + shares - 1) / shares; };
         if (S == 5 && M > 16 && slowest(4) == slowest(5) && tuning_get(TUNE_DECODE_SPLIT) <= 0) S = 4;
     } else {
@@ -435,8 +435,7 @@ static DecodePlan plan_small(int q, int M, int K, int N, int native, bool whole 
     }
     pl.S = S;
     // vectors of four rows per tile: up to 16 rows only the groups of four that exist, beyond whole tiles of 16 rows
-    // (all of 64 rows in tiles of 128 columns are as many as 32 in tiles of 256)
-    const size_t nvec = M <= 16 ? (size_t)pl.tile_n * ((M + 3) / 4) : (size_t)2048;
+    const size_t nvec = (size_t)pl.tile_n * (M <= 16 ? (M + 3) / 4 : M > 32 && narrow ? 16 : 8);
     pl.wide = wide;
     pl.slices = slices;
     pl.partial_bytes = S > 1 ? (size_t)pl.tiles * slices * S * nvec * 16 : 0;
@@ -468,26 +467,35 @@ DecodePlan plan_decode(int q, int M, int K, int N, int native)
     return p16.est_us < p32.est_us ? p16 : p32;
 }
 
-// Dense weights at 33 .. 64 rows, which the plan above shares out in slices of 32 rows by tiles of 256 columns, each slice reading the matrix: all rows in
-// one workgroup by tiles of 128, about as many workgroups, which read it once.  us at 33 / 64 rows, slices (or the LDS ring, which took most matrices from
-// 26e6 weights on) -> one pass: 4096 x 11008 30.5 / 31.0 -> 26.4 / 27.0, 4096 x 22016 54.8 / 55.9 -> 44.9 / 47.4, 5120 x 5120 23.7 / 24.5 -> 18.2 / 18.7,
-// 5120 x 27648 71.3 / 72.0 -> 58.0 / 61.3, 13824 x 5120 45.6 / 46.7 -> 34.9 / 36.3, 11008 x 4096 26.6 / 27.2 -> 24.2 / 25.3, 6144 x 4096 17.1 / 17.7 ->
-// 16.8 / 17.3.  A wave then walks a quarter of the part instead of half, but a workgroup loads and hands on twice the rows: where a part has up to 16 k-steps
-// (4096 x 4096 13.6 -> 14.2, 1024 x 4096 8.2 -> 9.0, 512 x 2048 7.1 -> 7.9) that gains only by more workgroups (2048 x 5120, 200 -> 240: 12.8 -> 11.9;
-// 4096 x 3072, 192 -> 240: 13.7 -> 13.1; 3072 x 3072 the same, 11.7 -> 11.4).  Where rows do not start on cache lines, a piece of 256 bytes touches three lines
-// instead of two, which a chip two thirds full does not hide (4224 x 11016, 174 workgroups, 31.2 / 32.2 -> 31.7 / 34.2; 5120 x 13832, 218, 41.9 / 42.3 -> 38.0 / 40.5;
-// 8192 x 3640, 232, 26.9 / 27.6 -> 21.6 / 21.5).  small = 0: not here.
-DecodePlan plan_one_pass(int M, int K, int N)
+// Dense weights in column tiles of 128 instead of 256 (small = 0: not here).  Up to 32 rows a workgroup loads half as many columns, which for the same number of
+// workgroups takes half the splits, and a tile count that fits the chip better or, for matrices of few columns (at most 16 splits), up to twice the workgroups; but
+// its reads are pieces of 256 bytes of a row.  us, tiles of 256 -> of 128:
+//   - more workgroups, at 1 / 7 / 24 rows: 8192 x 1024 (60 -> 120) 9.9 / 10.1 / 12.4 -> 8.1 / 8.0 / 9.55; 4096 x 1024 7.0 / 7.2 / 8.9 -> 5.8 / 5.8 / 7.1; 8192 x 2048 (120 -> 240)
+//     11.3 / 11.5 / 14.2 -> 9.9 / 9.7 / 11.4; 14336 x 5120 (200 -> 240) 31.9 / 32.4 / 36.2 -> 29.6 / 28.8 / 31.2; 5120 x 5120 14.5 -> 12.7 at 7; 1024 x 1024 (32 -> 64) 5.0 / 5.1 / 6.6 ->
+//     4.7 / 4.8 / 5.9; 2048 x 2048 5.8 / 5.9 / 7.5 -> 5.5 / 5.6 / 7.0; not where the few splits start whole megabytes apart (see above: 4096 x 4096 9.75 / 9.9 -> 10.0 / 9.8);
+//   - about as many: beyond 16 rows, where the hand-over is the larger, with up to 48 k-steps to a part (3584 x 3584 at 24 rows 11.0 -> 10.3, 6144 x 6144 19.8 -> 19.3; 74 steps
+//     of 18944 x 3584 29.75 -> 30.2, 80 of 5120 x 13824 31.3 -> 33.8); below, 0.96 .. 1.05;
+//   - fewer: 1.03 .. 1.10 (4096 x 12288, 240 -> 192, 20.8 -> 22.7 at 7 rows).
+// Beyond 32 rows the plan above has slices of 32 rows, each of which reads the matrix; here all rows are in one workgroup, and it is read once.  us at 33 / 64 rows, slices (or the LDS ring,
+// which took most matrices from 26e6 weights on) -> one pass: 4096 x 11008 30.5 / 31.0 -> 26.4 / 27.0, 4096 x 22016 54.8 / 55.9 -> 44.9 / 47.4, 5120 x 5120 23.7 / 24.5 -> 18.2 / 18.7,
+// 5120 x 27648 71.3 / 72.0 -> 58.0 / 61.3, 13824 x 5120 45.6 / 46.7 -> 34.9 / 36.3, 11008 x 4096 26.6 / 27.2 -> 24.2 / 25.3, 6144 x 4096 17.1 / 17.7 -> 16.8 / 17.3.  But a workgroup loads
+// and hands on twice the rows: where a part has up to 16 k-steps (4096 x 4096 13.6 -> 14.2, 1024 x 4096 8.2 -> 9.0, 512 x 2048 7.1 -> 7.9) that gains only by more workgroups
+// (2048 x 5120, 200 -> 240: 12.8 -> 11.9; 4096 x 3072, 192 -> 240: 13.7 -> 13.1; 3072 x 3072 the same, 11.7 -> 11.4).  Where rows do not start on cache lines, a piece of 256 bytes touches
+// three lines instead of two, which a chip two thirds full does not hide (4224 x 11016, 174 workgroups, 31.2 / 32.2 -> 31.7 / 34.2; 5120 x 13832, 218, 41.9 / 42.3 -> 38.0 / 40.5).
+DecodePlan plan_narrow(int M, int K, int N)
 {
-    if (M <= 32 || M > 64) return DecodePlan{};
-    const DecodePlan sliced = plan_decode(0, M, K, N);
-    if (!sliced.small) return DecodePlan{};
+    if (M > 64) return DecodePlan{};
+    const DecodePlan wide = plan_decode(0, M, K, N);
+    if (!wide.small) return DecodePlan{};
     const DecodePlan pl = plan_small(0, M, K, N, 0, true);
-    if (pl.partial_bytes > kSlotBytes || (pl.S > 1 && (pl.tiles > 256 || sliced.S == 1)) || pl.tiles > 65535) return DecodePlan{};   // (no workspace where none was asked for)
-    const int steps = (K / 32 + pl.S - 1) / pl.S;
-    if (N % 64 != 0 && pl.S > 1 && pl.tiles * pl.S < 192) return DecodePlan{};
-    const bool more = 8 * pl.tiles * pl.S >= 9 * sliced.tiles * sliced.slices * sliced.S;
-    return steps > 16 || (steps > 8 && more) ? pl : DecodePlan{};
+    if (pl.partial_bytes > kSlotBytes || (pl.S > 1 && (pl.tiles > 256 || wide.S == 1)) || pl.tiles > 65535) return DecodePlan{};   // (no workspace where none was asked for)
+    const int  T = K / 32, steps = (T + pl.S - 1) / pl.S, wgs = pl.tiles * pl.S, wgs_wide = wide.tiles * wide.slices * wide.S;
+    const bool more = 8 * wgs >= 9 * wgs_wide;
+    bool take;
+    if (M > 32) take = (steps > 16 || (steps > 8 && more)) && !(N % 64 != 0 && pl.S > 1 && wgs < 192);
+    else if (more) take = M > 16 || pl.S >= 12 || steps < 16 || T % pl.S != 0 || (long long)steps * N * 64 % (1 << 20) != 0;
+    else take = M > 16 && 16 * wgs >= 15 * wgs_wide && steps <= 48;
+    return take ? pl : DecodePlan{};
 }
 
 hipError_t launch_decode(int q, const DecodeArgs& a, hipStream_t st)

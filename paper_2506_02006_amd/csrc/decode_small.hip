@@ -1232,8 +1232,9 @@ __global__ __launch_bounds__(kWideWaves * 64) void decode_wide_kernel(
 // consecutive rows, pairs the 16-bit values of rows 2 q, 2 q + 1 column by column (v_perm_b32: the MFMA
 // wants 8 consecutive k of one column), and the accumulators are the running results.  MT: tiles of 16
 // rows per slice (1: M <= 16).  A k-step is 8 KB per wave, three of them in flight.
-// MT = 4: all of 33 .. 64 rows in one slice, so that the matrix is read once (plan_one_pass says where).  The four waves then take a quarter of K each over 128
-// columns: the accumulators fill as many registers as those of 32 rows x 256 columns would twice over, and no two waves load the same x.  x comes in groups of 64 k, half of the
+// CW = 1: column tiles of 128, each of the four waves takes a quarter of K over all of them (CW = 2: half of K over 128 of 256 columns).  No two waves load the
+// same x then, and as half as many splits fill the chip, a hand-over moves half as much (plan_narrow says where).
+// MT = 4 (CW = 1 only): all of 33 .. 64 rows in one slice, so that the matrix is read once.  x comes in groups of 64 k, half of the
 // next one requested in each of its two steps: whole groups of 128 k, or both halves at once, do not fit the registers beside three k-steps of weights, and what
 // was spilled of them at the start held the first weights back (4096 x 4096 17.0 us instead of 14.1, 5120 x 5120 19.6 instead of 18.7); groups of 32 k, half a
 // cache line of each row, read x twice (5120 x 27648 at 64 rows 69.5 us instead of 61.3).
@@ -1246,7 +1247,7 @@ struct DenseStage {
     u32x4 r[8];                                  // row 8 b + i of the k-step: the lane's 8 columns
 };
 
-template <int MT, bool BF, bool STEPS>
+template <int MT, bool BF, bool STEPS, int CW>
 __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     const uint32_t* w, const void* x_all, const void*, const uint32_t*, int K, int N, int ms, int qr,
     int tiles_sl, int inv_s, SmallTail t)
@@ -1264,7 +1265,7 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void decode_dense_kernel(
     MORPH_TICK(0);                                       // kernel entry
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int CW = MT == 4 ? 1 : 2, KH = kSmWaves / CW;   // waves side by side, and shares of K
+    constexpr int KH = kSmWaves / CW;                    // shares of K among the waves (CW: waves side by side)
     constexpr int TW = 128 * CW;                         // columns of a tile
     const int kh = wave / CW, ch = wave % CW;
     const int c = lane & 15, b = lane >> 4;
@@ -1455,10 +1456,13 @@ hipError_t launch_small_m(const SmallArgs& a, hipStream_t st)
         return launch_small_with(decode_small8_kernel<4, BF>, kSmWaves, a, st);
     }
     if (a.dense) {
-        if (a.M > 32 && a.slices == 1) return launch_small_with(decode_dense_kernel<4, BF, true>, kSmWaves, a, st, true);
+        if (a.narrow) {
+            if (a.M <= 16) return launch_small_with(decode_dense_kernel<1, BF, true, 1>, kSmWaves, a, st, true);
+            return a.M <= 32 ? launch_small_with(decode_dense_kernel<2, BF, true, 1>, kSmWaves, a, st, true) : launch_small_with(decode_dense_kernel<4, BF, true, 1>, kSmWaves, a, st, true);
+        }
         if (dense_by_steps(a.M, a.K, a.S, a.tiles))
-            return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, true>, kSmWaves, a, st, true) : launch_small_with(decode_dense_kernel<2, BF, true>, kSmWaves, a, st, true);
-        return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, false>, kSmWaves, a, st) : launch_small_with(decode_dense_kernel<2, BF, false>, kSmWaves, a, st);
+            return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, true, 2>, kSmWaves, a, st, true) : launch_small_with(decode_dense_kernel<2, BF, true, 2>, kSmWaves, a, st, true);
+        return a.M <= 16 ? launch_small_with(decode_dense_kernel<1, BF, false, 2>, kSmWaves, a, st) : launch_small_with(decode_dense_kernel<2, BF, false, 2>, kSmWaves, a, st);
     }
     if (a.native) {
         if (a.wide && a.M <= 4)  return launch_small_with(decode_wide_kernel<1, 1, BF>, kWideWaves, a, st);
@@ -1482,7 +1486,7 @@ hipError_t launch_decode_small(const SmallArgs& a, hipStream_t st)
 {
     if (a.M < 1 || a.M > 64 || a.S < 1 || a.S > 16 || a.S > a.K / kGroup || a.tiles < 1 || a.tiles > 65535 || a.K / kGroup > 65535) return hipErrorInvalidValue;
     if (a.wide && !a.native) return hipErrorInvalidValue;
-    if (a.slices != (a.M > 32 ? 2 : 1) && !(a.dense && a.M > 32 && a.slices == 1)) return hipErrorInvalidValue;
+    if (a.slices != (a.M > 32 && !a.narrow ? 2 : 1) || (a.narrow && !a.dense)) return hipErrorInvalidValue;
     if (a.S > 1 && a.tiles * a.slices > 256) return hipErrorInvalidValue;     // flags for 256 (tile, slice) pairs
     if (a.dense && a.native) return hipErrorInvalidValue;
     if (a.w8 && (a.dense || a.native || a.wide || a.M > 16)) return hipErrorInvalidValue;

@@ -71,7 +71,7 @@ constexpr int kSmallCtlInts  = 96;
 // q: 0 = fp16, 1 = 4-bit, 2 = 8-bit codes (the MORPH_KIND_* values)
 // native: the 4-bit codes are in the native storage order (q = 1 only)
 DecodePlan plan_decode(int q, int M, int K, int N, int native = 0);
-DecodePlan plan_one_pass(int M, int K, int N);   // dense, 33 .. 64 rows
+DecodePlan plan_narrow(int M, int K, int N);     // dense weights, up to 64 rows: tiles of 128 columns
 hipError_t launch_decode(int q, const DecodeArgs& a, hipStream_t st);
 
 // ---- 4-bit weights, M <= 16 (decode_small.hip) ----
@@ -85,8 +85,9 @@ struct SmallArgs {
     int*        ctl;       // kSmallCtlInts per tile: departure counter, flags, tags; zero on entry, zero on exit (S > 1)
     int         M, K, N;
     int         S;         // workgroups sharing one column tile (1 .. 16)
-    int         tiles;     // column tiles of 256 (8-bit codes, and dense weights with more than 32 rows in one slice: of 128)
-    int         slices;    // slices of 32 rows, 2 beyond 32 rows; dense weights: or all rows in one
+    int         tiles;     // column tiles of 256 (8-bit codes, narrow: of 128)
+    int         slices;    // slices of 32 rows: 2 beyond 32 rows, but narrow
+    int         narrow;    // dense weights: column tiles of 128, up to 64 rows in one slice (plan_narrow)
     int         polls;     // looks at the others' flags before a workgroup gives up
     int         far;       // hand-over always written through to memory, never left in an L2 (test hook)
     int         bf;
