@@ -481,7 +481,10 @@ DecodePlan plan_decode(int q, int M, int K, int N, int native)
 // 5120 x 27648 71.3 / 72.0 -> 58.0 / 61.3, 13824 x 5120 45.6 / 46.7 -> 34.9 / 36.3, 11008 x 4096 26.6 / 27.2 -> 24.2 / 25.3, 6144 x 4096 17.1 / 17.7 -> 16.8 / 17.3.  But a workgroup loads
 // and hands on twice the rows: where a part has up to 16 k-steps (4096 x 4096 13.6 -> 14.2, 1024 x 4096 8.2 -> 9.0, 512 x 2048 7.1 -> 7.9) that gains only by more workgroups
 // (2048 x 5120, 200 -> 240: 12.8 -> 11.9; 4096 x 3072, 192 -> 240: 13.7 -> 13.1; 3072 x 3072 the same, 11.7 -> 11.4).  Where rows do not start on cache lines, a piece of 256 bytes touches
-// three lines instead of two, which a chip two thirds full does not hide (4224 x 11016, 174 workgroups, 31.2 / 32.2 -> 31.7 / 34.2; 5120 x 13832, 218, 41.9 / 42.3 -> 38.0 / 40.5).
+// three lines instead of two, which a chip two thirds full does not hide (4224 x 11016, 174 workgroups, 31.2 / 32.2 -> 31.7 / 34.2; 5120 x 13832, 218, 41.9 / 42.3 -> 38.0 / 40.5;
+// 8064 x 12192, 192, 51.3 / 52.1 -> 49.1 / 55.0; 7296 x 20488, 161 with 228 k-steps each, 91.7 / 92.8 -> 83.0 / 95.5, 4096 x 20488, 128 k-steps, 54.6 / 55.7 -> 47.9 / 52.2).  And up to 160 workgroups leave matrices that the ring takes
+// to it: tiles of 256 columns still come three to a tile there (4096 x 18432, 144 workgroups against 216, 42.9 / 43.8 -> 44.2 / 48.0; 7296 x 18432 67.9 / 67.9 -> 76.8 / 84.2; 2048 x 17000, 133, 26.2 / 27.5
+// -> 27.4 / 28.5; 4096 x 20488, 161 against 162, above; 1280 x 16792, which the ring does not take, 26.8 / 26.6 -> 18.8 / 19.6).
 DecodePlan plan_narrow(int M, int K, int N)
 {
     if (M > 64) return DecodePlan{};
@@ -492,7 +495,7 @@ DecodePlan plan_narrow(int M, int K, int N)
     const int  T = K / 32, steps = (T + pl.S - 1) / pl.S, wgs = pl.tiles * pl.S, wgs_wide = wide.tiles * wide.slices * wide.S;
     const bool more = 8 * wgs >= 9 * wgs_wide;
     bool take;
-    if (M > 32) take = (steps > 16 || (steps > 8 && more)) && !(N % 64 != 0 && pl.S > 1 && wgs < 192);
+    if (M > 32) take = (steps > 16 || (steps > 8 && more)) && !(N % 64 != 0 && wgs <= 192 && (pl.S > 1 || steps > 128)) && !(wgs <= 160 && (double)K * N >= 26e6);
     else if (more) take = M > 16 || pl.S >= 12 || steps < 16 || T % pl.S != 0 || (long long)steps * N * 64 % (1 << 20) != 0;
     else take = M > 16 && 16 * wgs >= 15 * wgs_wide && steps <= 48;
     return take ? pl : DecodePlan{};

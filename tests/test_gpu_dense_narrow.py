@@ -22,10 +22,10 @@ HOOKS = {"plain": None, "recompute": ("TUNE_DECODE_SCATTER", 3), "far": ("TUNE_S
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16], ids=["fp16", "bf16"])
 @pytest.mark.parametrize("hook", list(HOOKS))
-# beyond 32 rows: sixteen parts of 17 and 18 k-steps (quarters of four and five) on one column group and on one tile and a bit; ten parts of fourteen; one part of
+# beyond 32 rows: sixteen parts of 17 and 18 k-steps (quarters of four and five) on half a tile and on one tile and a half; ten parts of fourteen; one part of
 # twenty, no hand-over; two parts of 34, off cache lines; rows at both ends of the range and on both sides of 48 = three tiles of rows.  Up to 32: parts of four
 # k-steps, one to a wave; fifteen parts; parts of five to seven; one row, a full tile of rows, one more than that, two full tiles
-@pytest.mark.parametrize("M,K,N", [(33, 8832, 8), (64, 8832, 136), (47, 4480, 2056), (48, 4480, 2056), (49, 640, 16400), (64, 2176, 13832),
+@pytest.mark.parametrize("M,K,N", [(33, 8832, 64), (64, 8832, 192), (47, 4480, 2112), (48, 4480, 2112), (49, 640, 16400), (64, 2176, 13832),
                                    (1, 8192, 1032), (5, 512, 136), (16, 768, 776), (17, 1280, 5128), (32, 4480, 5120), (24, 896, 8968)])
 def test_tiles_of_128_columns(B, M, K, N, hook, dtype):
     g = torch.Generator(device="cuda").manual_seed(M + K + N)
