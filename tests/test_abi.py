@@ -292,33 +292,53 @@ def test_decode_layout_fits_the_device_at_once(L):
     result, six to eight times slower: measured 49 us instead of 7 on a 5120 x 5120 matrix before this was checked.)"""
     plan = (ctypes.c_int * 5)()
     assert L.morph_plan_decode(1, 1, 4096, 4096, None) == 1
-    seen = 0
+    seen = narrows = 0
     for kind in (0, 1, 3):                                  # fp16, W4A16, W4A16 in native order
         for M in (1, 4, 8, 16, 17, 32, 33, 64):
             for K in (128, 1024, 4096, 5120, 11008, 14336):
                 for N in list(range(8, 8200, 248)) + [4096, 5120, 6144, 12288, 13824, 15360, 22016, 27648, 28672]:
                     assert L.morph_plan_decode(kind, M, K, N, plan) == 0, (kind, M, K, N)
-                    small, tiles, S, slices, wide = list(plan)
+                    small, tiles, S, slices, how = list(plan)
                     if not small:
                         continue
                     seen += 1
-                    assert tiles == (N + 255) // 256 and S >= 1 and slices == (2 if M > 32 else 1)
+                    narrow = how == 2                       # dense weights in tiles of 128 columns, all rows in one workgroup
+                    narrows += narrow
+                    width = 128 if narrow else 256
+                    assert tiles == (N + width - 1) // width and S >= 1 and slices == (2 if M > 32 and not narrow else 1) and (kind == 0 or not narrow)
                     if S > 1:
                         assert tiles * S * slices <= 256, (kind, M, K, N, list(plan))
                         assert ((tiles + 7) // 8) * S * slices <= 32, (kind, M, K, N, list(plan))
-    assert seen > 3000
+    assert seen > 3000 and narrows > 500
 
 
 @pytest.mark.parametrize("M,K,N,S", [
-    (7, 128, 264, 1), (7, 384, 264, 1), (7, 512, 264, 4), (7, 1024, 4096, 8), (64, 2048, 2048, 16), (7, 11008, 4096, 16),      # four k-steps to a workgroup
-    (7, 4096, 4096, 13), (32, 4096, 4096, 13), (64, 4096, 2048, 13), (1, 2048, 4096, 13), (7, 1536, 4096, 9), (32, 1920, 4096, 12),
-    (7, 8192, 4096, 15), (32, 14336, 4096, 15), (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15),
-    (32, 8192, 1024, 16), (1, 12288, 2048, 16), (32, 12288, 2048, 16), (64, 12288, 2048, 16), (7, 16384, 1024, 16), (32, 8192, 3072, 16),   # a longer part costs more
-    (33, 768, 6144, 4), (32, 1024, 12288, 4), (48, 1024, 5120, 4), (16, 1024, 12288, 5), (40, 2048, 5120, 5),                 # four are summed in one go
-    (7, 4096, 1024, 16), (7, 5120, 4096, 16), (7, 5120, 5120, 10)])                                                               # half megabytes do not show
+    (64, 2048, 2048, 16), (7, 11008, 4096, 16), (7, 5120, 4096, 16),                         # four k-steps to a workgroup
+    (7, 4096, 4096, 13), (64, 4096, 2048, 13), (7, 8192, 4096, 15), (32, 14336, 4096, 15),   # not whole megabytes apart
+    (33, 768, 6144, 4), (48, 1024, 5120, 4), (16, 1024, 12288, 5)])                          # four are summed in one go
 def test_dense_splits(L, M, K, N, S):
     """How many workgroups share K of a dense linear: uneven splits where even ones would start whole megabytes apart and the workgroups' parts are short or the
     chip is full, even ones elsewhere."""
     plan = (ctypes.c_int * 5)()
     assert L.morph_plan_decode(0, M, K, N, plan) == 0
-    assert plan[0] == 1 and plan[2] == S, list(plan)
+    assert list(plan) == [1, (N + 255) // 256, S, 2 if M > 32 else 1, 0]
+
+
+@pytest.mark.parametrize("M,K,N,S", [
+    (7, 128, 264, 1), (7, 384, 264, 1), (7, 512, 264, 4), (7, 1024, 4096, 8), (32, 4096, 4096, 8), (1, 2048, 4096, 8), (7, 1536, 4096, 8), (32, 1920, 4096, 8),
+    (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15), (32, 8192, 1024, 15), (1, 12288, 2048, 15), (32, 12288, 2048, 15),
+    (64, 12288, 2048, 15), (7, 16384, 1024, 16), (32, 8192, 3072, 10), (32, 1024, 12288, 2), (40, 2048, 5120, 6), (7, 4096, 1024, 16), (7, 5120, 5120, 6),
+    (64, 5120, 27648, 1), (64, 4096, 22016, 1), (64, 13824, 5120, 6)])                       # (the LDS ring took these before there were such tiles)
+def test_dense_tiles_of_128_columns(L, M, K, N, S):
+    """What is asked for is the plan that runs: dense linears in tiles of 128 columns are answered as such, at 33 to 64 rows too."""
+    plan = (ctypes.c_int * 5)()
+    assert L.morph_plan_decode(0, M, K, N, plan) == 0
+    assert list(plan) == [1, (N + 127) // 128, S, 1, 2]
+
+
+@pytest.mark.parametrize("M,K,N,small", [(33, 4096, 18432, 0), (64, 4224, 11016, 0), (32, 5120, 13824, 1), (7, 4096, 12288, 1), (7, 4224, 11016, 1), (64, 4096, 4096, 1)])
+def test_dense_linears_left_to_the_other_kernels(L, M, K, N, small):
+    """... and where tiles of 128 columns do not pay, by the LDS ring or in tiles of 256."""
+    plan = (ctypes.c_int * 5)()
+    assert L.morph_plan_decode(0, M, K, N, plan) == 0
+    assert plan[0] == small and plan[4] == 0
