@@ -39,8 +39,13 @@ extern "C" {
  * 2 = every wave an equal share of both; quantized kinds only).
  * 12 = the register-tiled kernel for at most 64 rows of 4-bit weights (2 = never: the general streaming kernels
  *      take them; 3 = only up to 16 rows; 4 = the native code order always through the four-wave kernels,
- *      never the eight-wave one; 5 = always through the eight-wave one).
+ *      never the eight-wave one; 5 = always through the eight-wave one; 6 = dense weights in column tiles of 128
+ *      wherever they can run that way, not only where it is faster).
  * 13 = that kernel's hand-over: 1 = written through to memory instead of kept in one XCD's L2.
+ * 14 = the LDS-ring kernels (1 = never; above, beyond 64 rows: always, in tiles of layout value / 16 and value % 16 tiles of
+ *      16 rows).  With any value dense weights of at most 64 rows keep out of column tiles of 128: the choice is between
+ *      tiles of 256 and the ring.
+ * 15 = workgroups that share K in the LDS-ring kernels beyond 64 rows.
  * A change alters morph_workspace_bytes(); size the workspace after setting. */
 int morph_set_tuning(int key, int value);
 

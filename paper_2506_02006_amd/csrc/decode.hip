@@ -492,6 +492,7 @@ DecodePlan plan_narrow(int M, int K, int N)
     if (!wide.small) return DecodePlan{};
     const DecodePlan pl = plan_small(0, M, K, N, 0, true);
     if (pl.partial_bytes > kSlotBytes || (pl.S > 1 && (pl.tiles > 256 || wide.S == 1)) || pl.tiles > 65535) return DecodePlan{};   // (no workspace where none was asked for)
+    if (tuning_get(TUNE_SMALL) == 6) return pl;
     const int  T = K / 32, steps = (T + pl.S - 1) / pl.S, wgs = pl.tiles * pl.S, wgs_wide = wide.tiles * wide.slices * wide.S;
     const bool more = 8 * wgs >= 9 * wgs_wide;
     bool take;

@@ -313,14 +313,21 @@ def test_decode_layout_fits_the_device_at_once(L):
 
 
 @pytest.mark.parametrize("M,K,N,S", [
-    (64, 2048, 2048, 16), (7, 11008, 4096, 16), (7, 5120, 4096, 16),                         # four k-steps to a workgroup
-    (7, 4096, 4096, 13), (64, 4096, 2048, 13), (7, 8192, 4096, 15), (32, 14336, 4096, 15),   # not whole megabytes apart
-    (33, 768, 6144, 4), (48, 1024, 5120, 4), (16, 1024, 12288, 5)])                          # four are summed in one go
+    (7, 128, 264, 1), (7, 384, 264, 1), (7, 512, 264, 4), (7, 1024, 4096, 8), (64, 2048, 2048, 16), (7, 11008, 4096, 16),      # four k-steps to a workgroup
+    (7, 4096, 4096, 13), (32, 4096, 4096, 13), (64, 4096, 2048, 13), (1, 2048, 4096, 13), (7, 1536, 4096, 9), (32, 1920, 4096, 12),
+    (7, 8192, 4096, 15), (32, 14336, 4096, 15), (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15),
+    (32, 8192, 1024, 16), (1, 12288, 2048, 16), (32, 12288, 2048, 16), (64, 12288, 2048, 16), (7, 16384, 1024, 16), (32, 8192, 3072, 16),   # a longer part costs more
+    (33, 768, 6144, 4), (32, 1024, 12288, 4), (48, 1024, 5120, 4), (16, 1024, 12288, 5), (40, 2048, 5120, 5),                 # four are summed in one go
+    (7, 4096, 1024, 16), (7, 5120, 4096, 16), (7, 5120, 5120, 10)])                                                               # half megabytes do not show
 def test_dense_splits(L, M, K, N, S):
-    """How many workgroups share K of a dense linear: uneven splits where even ones would start whole megabytes apart and the workgroups' parts are short or the
-    chip is full, even ones elsewhere."""
+    """How many workgroups share K of a dense linear in tiles of 256 columns: uneven splits where even ones would start whole megabytes apart and the workgroups'
+    parts are short or the chip is full, even ones elsewhere.  Key 14 = 1: the kernels without the LDS ring and the tiles of 128."""
     plan = (ctypes.c_int * 5)()
-    assert L.morph_plan_decode(0, M, K, N, plan) == 0
+    assert L.morph_set_tuning(14, 1) == 0
+    try:
+        assert L.morph_plan_decode(0, M, K, N, plan) == 0
+    finally:
+        assert L.morph_set_tuning(14, 0) == 0
     assert list(plan) == [1, (N + 255) // 256, S, 2 if M > 32 else 1, 0]
 
 
@@ -342,3 +349,16 @@ def test_dense_linears_left_to_the_other_kernels(L, M, K, N, small):
     plan = (ctypes.c_int * 5)()
     assert L.morph_plan_decode(0, M, K, N, plan) == 0
     assert plan[0] == small and plan[4] == 0
+
+
+@pytest.mark.parametrize("key,value,narrow", [(14, 1, 0), (14, 20, 0), (6, 32, 0), (6, 64, 1), (7, 32, 0), (12, 2, 0), (12, 3, 0), (12, 6, 1)])
+def test_keys_decide_about_tiles_of_128_columns(L, key, value, narrow):
+    """A linear that runs in tiles of 128 columns, and a key that names another kernel for it (40 rows: key 6 = 32 names the prefill kernels)."""
+    plan = (ctypes.c_int * 5)()
+    for M, K, N in ((40, 5120, 5120), (40, 4096, 22016)):
+        try:
+            assert L.morph_set_tuning(key, value) == 0
+            assert L.morph_plan_decode(0, M, K, N, plan) == 0
+        finally:
+            assert L.morph_set_tuning(key, 0) == 0
+        assert (plan[4] == 2) == narrow, list(plan)
