@@ -485,6 +485,12 @@ DecodePlan plan_decode(int q, int M, int K, int N, int native)
 // 8064 x 12192, 192, 51.3 / 52.1 -> 49.1 / 55.0; 7296 x 20488, 161 with 228 k-steps each, 91.7 / 92.8 -> 83.0 / 95.5, 4096 x 20488, 128 k-steps, 54.6 / 55.7 -> 47.9 / 52.2).  And up to 160 workgroups leave matrices that the ring takes
 // to it: tiles of 256 columns still come three to a tile there (4096 x 18432, 144 workgroups against 216, 42.9 / 43.8 -> 44.2 / 48.0; 7296 x 18432 67.9 / 67.9 -> 76.8 / 84.2; 2048 x 17000, 133, 26.2 / 27.5
 // -> 27.4 / 28.5; 4096 x 20488, 161 against 162, above; 1280 x 16792, which the ring does not take, 26.8 / 26.6 -> 18.8 / 19.6).
+// Beyond 256 tiles (32768 columns, K in one part) what counts is the rounds in which the compute units take the tiles, two of 128 columns to one of 256.  Up to 32 rows: fewer rounds pay
+// from 21 k-steps on (70000 columns, 3 halves against 4, at 1 / 24 rows: 1024 rows of K 36.2 / 42.4 -> 32.2 / 38.2, 512 18.9 / 22.4 -> 18.5 / 23.4; 151936 columns, 5 against 6: 4096 208.9 / 221.9 ->
+// 194.7 / 211.4, 640 37.3 / 43.2 -> 37.5 / 45.7), as many do not (5120 x 33024 72.0 / 80.0 -> 78.7 / 86.7, 1024 x 50304 18.7 / 21.1 -> 21.6 / 25.5, 4096 x 128256 24 rows 170.5 -> 183.5).  At 33 .. 64 rows
+// the ring reads the matrix once as well, in tiles of 256 (the slices twice).  Fewer rounds pay there too (33 / 64 rows: 4096 x 70000 176.0 / 179.9 -> 133.7 / 142.1, 768 x 98304 41.3 / 41.9 -> 37.1 / 39.3); as
+// many do from 48 k-steps on and on cache lines, if the last round of tiles of 256 leaves compute units idle (4096 x 33024 84.7 / 85.9 -> 71.1 / 74.7, 5120 x 64256 125.3 / 127.1 -> 111.5 / 119.4, 4096 x 128256
+// 208.3 / 213.9 -> 184.6 / 200.8, 1536 x 57344 41.2 / 41.8 -> 40.6 / 42.0; but 4096 x 131072 205.6 / 209.6 -> 202.7 / 217.8, 1024 x 33024 23.7 / 24.5 -> 24.9 / 26.0, 3072 x 33032 65.4 / 65.3 -> 65.6 / 69.7).
 DecodePlan plan_narrow(int M, int K, int N)
 {
     if (M > 64) return DecodePlan{};
@@ -496,7 +502,12 @@ DecodePlan plan_narrow(int M, int K, int N)
     const int  T = K / 32, steps = (T + pl.S - 1) / pl.S, wgs = pl.tiles * pl.S, wgs_wide = wide.tiles * wide.slices * wide.S;
     const bool more = 8 * wgs >= 9 * wgs_wide;
     bool take;
-    if (M > 32) take = (steps > 16 || (steps > 8 && more)) && !(N % 64 != 0 && wgs <= 192 && (pl.S > 1 || steps > 128)) && !(wgs <= 160 && (double)K * N >= 26e6);
+    if (const int cus = prefill_compute_units(); wgs > cus) {
+        auto rounds = [&](int n) { return (n + cus - 1) / cus; };
+        const bool ring  = M > 32 && (double)K * N >= 26e6;
+        const bool fewer = rounds(wgs) < 2 * rounds(ring ? wide.tiles : wgs_wide);
+        take = fewer ? steps > (M > 32 ? 16 : 20) : ring && steps >= 48 && N % 64 == 0 && wide.tiles % cus != 0;
+    } else if (M > 32) take = (steps > 16 || (steps > 8 && more)) && !(N % 64 != 0 && wgs <= 192 && (pl.S > 1 || steps > 128)) && !(wgs <= 160 && (double)K * N >= 26e6);
     else if (more) take = M > 16 || pl.S >= 12 || steps < 16 || T % pl.S != 0 || (long long)steps * N * 64 % (1 << 20) != 0;
     else take = M > 16 && 16 * wgs >= 15 * wgs_wide && steps <= 48;
     return take ? pl : DecodePlan{};

@@ -362,3 +362,15 @@ def test_keys_decide_about_tiles_of_128_columns(L, key, value, narrow):
         finally:
             assert L.morph_set_tuning(key, 0) == 0
         assert (plan[4] == 2) == narrow, list(plan)
+
+
+@pytest.mark.parametrize("M,K,N,narrow", [
+    (1, 5120, 33024, 0), (24, 4096, 33024, 0), (7, 1024, 50304, 0), (24, 4096, 49152, 0), (24, 4096, 128256, 0), (17, 1024, 256000, 0),        # two halves for one, four for two
+    (1, 1024, 70000, 1), (24, 4096, 81920, 1), (7, 4096, 151936, 1), (32, 640, 151936, 0), (24, 512, 70400, 0),                             # three for two, five for three; short parts
+    (33, 4096, 33024, 1), (64, 5120, 64256, 1), (64, 4096, 128256, 1), (64, 4096, 65536, 0), (33, 4096, 131072, 0), (64, 1024, 33024, 0),   # against the ring
+    (64, 3072, 33032, 0), (33, 3072, 70000, 1), (64, 768, 98304, 1), (33, 768, 33024, 1), (40, 4096, 32768, 1), (1, 4096, 32768, 0)])
+def test_dense_tiles_of_128_columns_beyond_the_compute_units(L, M, K, N, narrow):
+    """More tiles than compute units: workgroups that wait for a free one are no gain, fewer rounds of tiles are."""
+    plan = (ctypes.c_int * 5)()
+    assert L.morph_plan_decode(0, M, K, N, plan) == 0
+    assert (plan[4] == 2) == narrow, list(plan)
