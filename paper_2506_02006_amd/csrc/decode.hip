@@ -416,11 +416,13 @@ static DecodePlan plan_small(int q, int M, int K, int N, int native, bool narrow
             const bool short_part = T / S <= 16 && (apart & (apart - 1)) == 0 && (M <= 16 || pl.tiles * slices * S >= 128);
             if (takes_all || short_part) S -= T <= 128 ? 3 : 1;
         }
-        // The sum over up to four splits is read four wide, over more sixteen wide (finish_over_splits), which shows beyond 16 rows: four instead of five where the
-        // slowest half of the waves has no more to walk then (us, 5 -> 4: 768 x 6144 at 33 rows 9.2 -> 8.6, 1024 x 12288 at 32 11.8 -> 10.95; at 1 row 8.17, 8.15).
+        // The sum over up to four splits is read four wide, over five to eight eight wide (finish_over_splits), which shows a little beyond 16 rows: four instead of five where
+        // the slowest share of the waves has no more to walk then and parts are short (us, 5 -> 4: 768 x 12288 at 17 / 32 rows 9.4 / 9.55 -> 9.25 / 9.3, 1024 x 12288 11.0 / 10.95 -> 10.95 / 10.85; tiles of
+        // 128, 896 x 5248 at 17 / 64 rows 7.2 / 9.7 -> 7.05 / 9.45, 1408 x 5248 7.9 / 10.6 -> 7.8 / 10.4, but 2048 x 6144 at 17 rows 10.25 -> 10.6).  Not in slices of 32 rows
+        // (768 x 6144 at 33 / 64 rows 8.45 / 8.6 either way, 1024 x 6144 9.55 / 9.7 -> 9.8 / 9.85).
         const int shares = narrow ? 4 : 2;                // of a part among the waves
         auto slowest = [&](int s) { return ((T + s - 1) / s + shares - 1) / shares; };
-        if (S == 5 && M > 16 && slowest(4) == slowest(5) && tuning_get(TUNE_DECODE_SPLIT) <= 0) S = 4;
+        if (S == 5 && M > 16 && slices == 1 && T <= 48 && slowest(4) == slowest(5) && tuning_get(TUNE_DECODE_SPLIT) <= 0) S = 4;
     } else {
         S = split_for((M <= 16 && q != 0) ? T / 4 : halves);
     }

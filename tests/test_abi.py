@@ -317,7 +317,7 @@ def test_decode_layout_fits_the_device_at_once(L):
     (7, 4096, 4096, 13), (32, 4096, 4096, 13), (64, 4096, 2048, 13), (1, 2048, 4096, 13), (7, 1536, 4096, 9), (32, 1920, 4096, 12),
     (7, 8192, 4096, 15), (32, 14336, 4096, 15), (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15),
     (32, 8192, 1024, 16), (1, 12288, 2048, 16), (32, 12288, 2048, 16), (64, 12288, 2048, 16), (7, 16384, 1024, 16), (32, 8192, 3072, 16),   # a longer part costs more
-    (33, 768, 6144, 4), (32, 1024, 12288, 4), (48, 1024, 5120, 4), (16, 1024, 12288, 5), (40, 2048, 5120, 5),                 # four are summed in one go
+    (17, 768, 12288, 4), (32, 1024, 12288, 4), (33, 768, 6144, 5), (48, 1024, 5120, 5), (16, 1024, 12288, 5), (40, 2048, 5120, 5),   # four for five in one slice
     (7, 4096, 1024, 16), (7, 5120, 4096, 16), (7, 5120, 5120, 10)])                                                               # half megabytes do not show
 def test_dense_splits(L, M, K, N, S):
     """How many workgroups share K of a dense linear in tiles of 256 columns: uneven splits where even ones would start whole megabytes apart and the workgroups'
@@ -335,7 +335,7 @@ def test_dense_splits(L, M, K, N, S):
     (7, 128, 264, 1), (7, 384, 264, 1), (7, 512, 264, 4), (7, 1024, 4096, 8), (32, 4096, 4096, 8), (1, 2048, 4096, 8), (7, 1536, 4096, 8), (32, 1920, 4096, 8),
     (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15), (32, 8192, 1024, 15), (1, 12288, 2048, 15), (32, 12288, 2048, 15),
     (64, 12288, 2048, 15), (7, 16384, 1024, 16), (32, 8192, 3072, 10), (32, 1024, 12288, 2), (40, 2048, 5120, 6), (7, 4096, 1024, 16), (7, 5120, 5120, 6),
-    (64, 5120, 27648, 1), (64, 4096, 22016, 1), (64, 13824, 5120, 6)])                       # (the LDS ring took these before there were such tiles)
+    (64, 5120, 27648, 1), (64, 4096, 22016, 1), (64, 13824, 5120, 6), (17, 896, 5248, 4), (32, 1024, 6144, 4), (17, 2048, 6144, 5)])                       # (the LDS ring took these before there were such tiles)
 def test_dense_tiles_of_128_columns(L, M, K, N, S):
     """What is asked for is the plan that runs: dense linears in tiles of 128 columns are answered as such, at 33 to 64 rows too."""
     plan = (ctypes.c_int * 5)()
