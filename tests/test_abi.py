@@ -374,3 +374,17 @@ def test_dense_tiles_of_128_columns_beyond_the_compute_units(L, M, K, N, narrow)
     plan = (ctypes.c_int * 5)()
     assert L.morph_plan_decode(0, M, K, N, plan) == 0
     assert (plan[4] == 2) == narrow, list(plan)
+
+
+@pytest.mark.parametrize("M,K,N", [(24, 512, 20560), (32, 1408, 32768), (17, 1536, 30720)])
+def test_dense_linears_without_the_workspace_asked_for(L, M, K, N):
+    """Tiles of 128 columns with K in one part would do without a workspace; where the kernels by 256 cannot, none, a small one and one
+    off 16 bytes are refused all the same."""
+    plan = (ctypes.c_int * 5)()
+    assert L.morph_plan_decode(0, M, K, N, plan) == 0 and plan[4] == 2 and plan[2] == 1
+    need = L.morph_workspace_bytes(0, M, K, N)
+    assert need > 0
+    for f in (L.morph_linear_fp16, L.morph_linear_bf16):
+        assert f(FAKE, FAKE, FAKE, M, K, N, None, 0, None) == 4
+        assert f(FAKE, FAKE, FAKE, M, K, N, FAKE, 64, None) == 4
+        assert f(FAKE, FAKE, FAKE, M, K, N, FAKE + 8, need, None) == 3
