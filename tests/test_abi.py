@@ -293,23 +293,27 @@ def test_decode_layout_fits_the_device_at_once(L):
     plan = (ctypes.c_int * 5)()
     assert L.morph_plan_decode(1, 1, 4096, 4096, None) == 1
     seen = narrows = 0
-    for kind in (0, 1, 3):                                  # fp16, W4A16, W4A16 in native order
-        for M in (1, 4, 8, 16, 17, 32, 33, 64):
-            for K in (128, 1024, 4096, 5120, 11008, 14336):
-                for N in list(range(8, 8200, 248)) + [4096, 5120, 6144, 12288, 13824, 15360, 22016, 27648, 28672]:
-                    assert L.morph_plan_decode(kind, M, K, N, plan) == 0, (kind, M, K, N)
-                    small, tiles, S, slices, how = list(plan)
-                    if not small:
-                        continue
-                    seen += 1
-                    narrow = how == 2                       # dense weights in tiles of 128 columns, all rows in one workgroup
-                    narrows += narrow
-                    width = 128 if narrow else 256
-                    assert tiles == (N + width - 1) // width and S >= 1 and slices == (2 if M > 32 and not narrow else 1) and (kind == 0 or not narrow)
-                    if S > 1:
-                        assert tiles * S * slices <= 256, (kind, M, K, N, list(plan))
-                        assert ((tiles + 7) // 8) * S * slices <= 32, (kind, M, K, N, list(plan))
-    assert seen > 3000 and narrows > 500
+    for kind, key in ((0, 0), (1, 0), (3, 0), (0, 6)):      # fp16, W4A16, W4A16 in native order; fp16 in tiles of 128 columns wherever they can run
+        try:
+            assert L.morph_set_tuning(12, key) == 0
+            for M in (1, 4, 8, 16, 17, 32, 33, 64):
+                for K in (128, 1024, 4096, 5120, 11008, 14336):
+                    for N in list(range(8, 8200, 248)) + [4096, 5120, 6144, 12288, 13824, 15360, 22016, 27648, 28672]:
+                        assert L.morph_plan_decode(kind, M, K, N, plan) == 0, (kind, M, K, N)
+                        small, tiles, S, slices, how = list(plan)
+                        if not small:
+                            continue
+                        seen += 1
+                        narrow = how == 2                       # dense weights in tiles of 128 columns, all rows in one workgroup
+                        narrows += narrow
+                        width = 128 if narrow else 256
+                        assert tiles == (N + width - 1) // width and S >= 1 and slices == (2 if M > 32 and not narrow else 1) and (kind == 0 or not narrow)
+                        if S > 1:
+                            assert tiles * S * slices <= 256, (kind, M, K, N, list(plan))
+                            assert ((tiles + 7) // 8) * S * slices <= 32, (kind, M, K, N, list(plan))
+        finally:
+            L.morph_set_tuning(12, 0)
+    assert seen > 3000 and narrows > 2000
 
 
 @pytest.mark.parametrize("M,K,N,S", [
@@ -335,7 +339,8 @@ def test_dense_splits(L, M, K, N, S):
     (7, 128, 264, 1), (7, 384, 264, 1), (7, 512, 264, 4), (7, 1024, 4096, 8), (32, 4096, 4096, 8), (1, 2048, 4096, 8), (7, 1536, 4096, 8), (32, 1920, 4096, 8),
     (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15), (32, 8192, 1024, 15), (1, 12288, 2048, 15), (32, 12288, 2048, 15),
     (64, 12288, 2048, 15), (7, 16384, 1024, 16), (32, 8192, 3072, 10), (32, 1024, 12288, 2), (40, 2048, 5120, 6), (7, 4096, 1024, 16), (7, 5120, 5120, 6),
-    (64, 5120, 27648, 1), (64, 4096, 22016, 1), (64, 13824, 5120, 6), (17, 896, 5248, 4), (32, 1024, 6144, 4), (17, 2048, 6144, 5)])                       # (the LDS ring took these before there were such tiles)
+    (64, 5120, 27648, 1), (64, 4096, 22016, 1), (64, 13824, 5120, 6),                         # (the LDS ring took these before there were such tiles)
+    (17, 896, 5248, 4), (32, 1024, 6144, 4), (17, 2048, 6144, 5)])
 def test_dense_tiles_of_128_columns(L, M, K, N, S):
     """What is asked for is the plan that runs: dense linears in tiles of 128 columns are answered as such, at 33 to 64 rows too."""
     plan = (ctypes.c_int * 5)()
