@@ -2,6 +2,8 @@
 
 Bound, per element, against an fp64 product: fp32 sums of K products of at most K + 64 additions each off by 2^-24 of their magnitude, and y rounded to its
 16 bits by u |y| (and half the smallest subnormal, 2^-25).  So |y - ref| <= (K + 64) 2^-24 sum|x||w| + u |ref| + 2^-25."""
+import ctypes
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -32,6 +34,9 @@ def test_tiles_of_128_columns(B, M, K, N, hook, dtype):
     w = (torch.randn((K, N), generator=g, device="cuda") * 0.05).to(dtype)
     x = torch.randn((M, K), generator=g, device="cuda").to(dtype)
     fn = B.linear_fp16 if dtype == torch.float16 else B.linear_bf16
+    plan = (ctypes.c_int * 5)()
+    assert B.lib().morph_plan_decode(B.KIND_FP16, M, K, N, plan) == 0
+    assert list(plan[:2]) == [1, -(-N // 128)] and plan[4] == 2, "the planner leaves it to another kernel"
     out = torch.full((M + 1, N), 77.0, dtype=dtype, device="cuda")
     if HOOKS[hook]:
         B.set_tuning(getattr(B, HOOKS[hook][0]), HOOKS[hook][1])
