@@ -482,7 +482,9 @@ DecodePlan plan_decode(int q, int M, int K, int N, int native)
 // which took most matrices from 26e6 weights on) -> one pass: 4096 x 11008 30.5 / 31.0 -> 26.4 / 27.0, 4096 x 22016 54.8 / 55.9 -> 44.9 / 47.4, 5120 x 5120 23.7 / 24.5 -> 18.2 / 18.7,
 // 5120 x 27648 71.3 / 72.0 -> 58.0 / 61.3, 13824 x 5120 45.6 / 46.7 -> 34.9 / 36.3, 11008 x 4096 26.6 / 27.2 -> 24.2 / 25.3, 6144 x 4096 17.1 / 17.7 -> 16.8 / 17.3.  But a workgroup loads
 // and hands on twice the rows: where a part has up to 16 k-steps (4096 x 4096 13.6 -> 14.2, 1024 x 4096 8.2 -> 9.0, 512 x 2048 7.1 -> 7.9) that gains only by more workgroups
-// (2048 x 5120, 200 -> 240: 12.8 -> 11.9; 4096 x 3072, 192 -> 240: 13.7 -> 13.1; 3072 x 3072 the same, 11.7 -> 11.4).  Where rows do not start on cache lines, a piece of 256 bytes touches
+// (2048 x 5120, 200 -> 240: 12.8 -> 11.9; 4096 x 3072, 192 -> 240: 13.7 -> 13.1; 3072 x 3072 the same, 11.7 -> 11.4), and where split parts on a full chip (240 workgroups and more) have up to 22
+// (33 / 64 rows: 2816 x 8192 16.05 / 15.7 -> 16.5 / 16.25, 5632 x 4096 15.1 / 15.3 -> 15.8 / 16.0, 8192 x 2048 13.5 / 13.7 -> 14.2 / 14.15; but 24, 3072 x 8192, 17.2 / 17.0 -> 16.8 / 16.7, and on 198 workgroups
+// 18, 1664 x 8448 at 48, 14.1 -> 13.8).  Where rows do not start on cache lines, a piece of 256 bytes touches
 // three lines instead of two, which a chip two thirds full does not hide (4224 x 11016, 174 workgroups, 31.2 / 32.2 -> 31.7 / 34.2; 5120 x 13832, 218, 41.9 / 42.3 -> 38.0 / 40.5;
 // 8064 x 12192, 192, 51.3 / 52.1 -> 49.1 / 55.0; 7296 x 20488, 161 with 228 k-steps each, 91.7 / 92.8 -> 83.0 / 95.5, 4096 x 20488, 128 k-steps, 54.6 / 55.7 -> 47.9 / 52.2).  And up to 160 workgroups leave matrices that the ring takes
 // to it: tiles of 256 columns still come three to a tile there (4096 x 18432, 144 workgroups against 216, 42.9 / 43.8 -> 44.2 / 48.0; 7296 x 18432 67.9 / 67.9 -> 76.8 / 84.2; 2048 x 17000, 133, 26.2 / 27.5
@@ -502,14 +504,15 @@ DecodePlan plan_narrow(int M, int K, int N)
     if (pl.partial_bytes > kSlotBytes || (pl.S > 1 && (pl.tiles > 256 || wide.S == 1)) || pl.tiles > 65535) return DecodePlan{};   // (no workspace where none was asked for)
     if (tuning_get(TUNE_SMALL) == 6) return pl;
     const int  T = K / 32, steps = (T + pl.S - 1) / pl.S, wgs = pl.tiles * pl.S, wgs_wide = wide.tiles * wide.slices * wide.S;
+    const int  cus = prefill_compute_units();
     const bool more = 8 * wgs >= 9 * wgs_wide;
     bool take;
-    if (const int cus = prefill_compute_units(); wgs > cus) {
+    if (wgs > cus) {
         auto rounds = [&](int n) { return (n + cus - 1) / cus; };
         const bool ring  = M > 32 && (double)K * N >= 26e6;
         const bool fewer = rounds(wgs) < 2 * rounds(ring ? wide.tiles : wgs_wide);
         take = fewer ? steps > (M > 32 ? 16 : 20) : ring && steps >= 48 && N % 64 == 0 && wide.tiles % cus != 0;
-    } else if (M > 32) take = (steps > 16 || (steps > 8 && more)) && !(N % 64 != 0 && wgs <= 192 && (pl.S > 1 || steps > 128)) && !(wgs <= 160 && (double)K * N >= 26e6);
+    } else if (M > 32) take = (steps > (pl.S > 1 && 16 * wgs >= 15 * cus ? 22 : 16) || (steps > 8 && more)) && !(N % 64 != 0 && wgs <= 192 && (pl.S > 1 || steps > 128)) && !(wgs <= 160 && (double)K * N >= 26e6);
     else if (more) take = M > 16 || pl.S >= 12 || steps < 16 || T % pl.S != 0 || (long long)steps * N * 64 % (1 << 20) != 0;
     else take = M > 16 && 16 * wgs >= 15 * wgs_wide && steps <= 48;
     return take ? pl : DecodePlan{};

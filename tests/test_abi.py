@@ -337,10 +337,10 @@ def test_dense_splits(L, M, K, N, S):
 
 @pytest.mark.parametrize("M,K,N,S", [
     (7, 128, 264, 1), (7, 384, 264, 1), (7, 512, 264, 4), (7, 1024, 4096, 8), (32, 4096, 4096, 8), (1, 2048, 4096, 8), (7, 1536, 4096, 8), (32, 1920, 4096, 8),
-    (7, 8192, 2048, 15), (64, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15), (32, 8192, 1024, 15), (1, 12288, 2048, 15), (32, 12288, 2048, 15),
+    (7, 8192, 2048, 15), (7, 8192, 1024, 15), (64, 8192, 1024, 15), (32, 8192, 1024, 15), (1, 12288, 2048, 15), (32, 12288, 2048, 15),
     (64, 12288, 2048, 15), (7, 16384, 1024, 16), (32, 8192, 3072, 10), (32, 1024, 12288, 2), (40, 2048, 5120, 6), (7, 4096, 1024, 16), (7, 5120, 5120, 6),
     (64, 5120, 27648, 1), (64, 4096, 22016, 1), (64, 13824, 5120, 6),                         # (the LDS ring took these before there were such tiles)
-    (17, 896, 5248, 4), (32, 1024, 6144, 4), (17, 2048, 6144, 5)])
+    (17, 896, 5248, 4), (32, 1024, 6144, 4), (17, 2048, 6144, 5), (64, 3072, 8192, 4), (48, 1664, 8448, 3), (33, 640, 32768, 1)])
 def test_dense_tiles_of_128_columns(L, M, K, N, S):
     """What is asked for is the plan that runs: dense linears in tiles of 128 columns are answered as such, at 33 to 64 rows too."""
     plan = (ctypes.c_int * 5)()
@@ -348,7 +348,8 @@ def test_dense_tiles_of_128_columns(L, M, K, N, S):
     assert list(plan) == [1, (N + 127) // 128, S, 1, 2]
 
 
-@pytest.mark.parametrize("M,K,N,small", [(33, 4096, 18432, 0), (64, 4224, 11016, 0), (32, 5120, 13824, 1), (7, 4096, 12288, 1), (7, 4224, 11016, 1), (64, 4096, 4096, 1)])
+@pytest.mark.parametrize("M,K,N,small", [(33, 4096, 18432, 0), (64, 4224, 11016, 0), (32, 5120, 13824, 1), (7, 4096, 12288, 1), (7, 4224, 11016, 1), (64, 4096, 4096, 1),
+                                             (33, 2304, 8192, 1), (64, 4608, 4096, 1), (64, 8192, 2048, 1), (64, 1408, 16000, 1)])     # split parts of up to 22 k-steps on a full chip
 def test_dense_linears_left_to_the_other_kernels(L, M, K, N, small):
     """... and where tiles of 128 columns do not pay, by the LDS ring or in tiles of 256."""
     plan = (ctypes.c_int * 5)()
