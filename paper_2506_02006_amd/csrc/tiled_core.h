@@ -203,14 +203,6 @@ __device__ __forceinline__ void tiled_finish(const TiledTail& t, int S, const Ti
     pass();
     put_all(p.sp, 0, G::kVecs);
     MORPH_TICK(4);
-    // Byte offset of split q (beyond S: of the last one, not added), made while the stores are under way (see finish_over_splits).
-    uint32_t from[16];
-#pragma unroll
-    for (int q = 0; q < 16; q++) {
-        from[q] = (uint32_t)(q < S ? q : S - 1) * slot_bytes;
-        asm volatile("" : "+s"(from[q]));
-    }
-    const __amdgpu_buffer_rsrc_t ry = make_rsrc(y, (uint32_t)M * (uint32_t)N * 2u);
     wait_stores();
     __syncthreads();
     MORPH_TICK(5);
@@ -246,8 +238,8 @@ __device__ __forceinline__ void tiled_finish(const TiledTail& t, int S, const Ti
         wait_stores();
         __syncthreads();
     }
-    auto get = [&](int q, int vec) __attribute__((always_inline)) {
-        return __builtin_amdgcn_raw_buffer_load_b128(rp, (uint32_t)vec * 16u, from[q], kAuxSystemScope);
+    auto get = [&](int q, int vec) __attribute__((always_inline)) {  // (splits that do not exist lie past the buffer: zeros)
+        return __builtin_amdgcn_raw_buffer_load_b128(rp, q < S ? (uint32_t)q * slot_bytes + (uint32_t)vec * 16u : 0xFFFFFFF0u, 0, kAuxSystemScope);
     };
     for (int v = v0 + tid; v < v1; v += G::kThreads) {
         const int blk = quads ? v >> 6 : v >> 8, ln = v & 63;
@@ -266,9 +258,11 @@ __device__ __forceinline__ void tiled_finish(const TiledTail& t, int S, const Ti
 #pragma unroll
                 for (int e = 0; e < 4; e++)
                     if (q < S) acc[e] += bit_cast<f32x4>(f[q][e]);
+            if (col < N) {
 #pragma unroll
-            for (int r = 0; r < 4; r++)
-                __builtin_amdgcn_raw_buffer_store_b64(u32x2{pack2(acc[0][r], acc[1][r]), pack2(acc[2][r], acc[3][r])}, ry, col < N && row + r < M ? (uint32_t)((row + r) * N + col) * 2u : 0xFFFFFF00u, 0, 0);
+                for (int r = 0; r < 4; r++)
+                    if (row + r < M) *reinterpret_cast<u32x2*>(y + (size_t)(row + r) * N + col) = u32x2{pack2(acc[0][r], acc[1][r]), pack2(acc[2][r], acc[3][r])};
+            }
         } else {
             u32x4 f[16];
 #pragma unroll
@@ -278,9 +272,11 @@ __device__ __forceinline__ void tiled_finish(const TiledTail& t, int S, const Ti
             for (int q = 0; q < 16; q++)
                 if (q < S) acc += bit_cast<f32x4>(f[q]);
             const int e = (v >> 6) & 3;
+            if (col < N) {
 #pragma unroll
-            for (int r = 0; r < 4; r++)
-                __builtin_amdgcn_raw_buffer_store_b16(narrow16<BF>(acc[r]), ry, col < N && row + r < M ? (uint32_t)((row + r) * N + col + e) * 2u : 0xFFFFFF00u, 0, 0);
+                for (int r = 0; r < 4; r++)
+                    if (row + r < M) y[(size_t)(row + r) * N + col + e] = narrow16<BF>(acc[r]);
+            }
         }
     }
     MORPH_TICK(7);
